@@ -33,7 +33,7 @@ def build(verbose: bool = False) -> str:
     tmp = LIB + ".tmp"
     cmd = [hipcc(), f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-shared",
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-           "-Wall", "-Wno-unused-result", "-I", os.path.join(ROOT, "include"),
+           "-Wall", "-Wno-unused-result", "-Wno-inline-asm", "-I", os.path.join(ROOT, "include"),
            *SOURCES, "-o", tmp]
     res = subprocess.run(cmd, capture_output=True, text=True)
     noise = "is not a recognized feature for this target"

@@ -9,13 +9,13 @@
 //    token-major [16][D]; V blocks are stored dimension-major [D][16] so the
 //    attention kernel can feed them to the matrix cores without a transpose.
 //  * paged_attn: causal grouped-query attention of the suffix queries.  A
-//    work item is 256 query columns of one (request, kv head); a column is a
+//    work item is 128 query columns of one (request, kv head); a column is a
 //    (token, q head of the group) pair, so the G heads of a group share every
-//    K/V tile.  The kernel is persistent (one 8-wave workgroup per CU) and
-//    takes items from per-XCD queues (with no more items than CUs, one item
-//    per workgroup by position).  64-key tiles (4 pool blocks) stream
-//    through a 4-tile ring in LDS, filled by direct global-to-LDS loads
-//    issued a tile step ahead of use.  Per tile and wave:
+//    K/V tile.  The kernel is persistent: two 4-wave workgroups per CU (three
+//    at head size 64) take items by position and, the uneven rest, from
+//    per-XCD counters.  64-key tiles (4 pool blocks) stream through two K and
+//    two V buffers in LDS, filled by direct global-to-LDS loads issued a tile
+//    step ahead of use.  Per tile and wave:
 //      S^T = K Q^T   on v_mfma_f32_32x32x16_bf16 (a lane owns one column),
 //      causal mask, online softmax in fp32 on exp2 with the scale folded in:
 //      the exponentials are taken against the running column max, and the
@@ -25,11 +25,20 @@
 //      O^T += V^T P^T on the same MFMA, P taken straight from the S^T
 //      accumulators (K rows are staged in a permuted order that makes the
 //      accumulator layout of S^T equal the operand layout P^T needs).
-//    The two waves sharing a SIMD run these steps half a tile apart, so one
-//    feeds the matrix core while the other computes the softmax.
+//    What bounds it: on large batches the power limit (zeros for inputs run
+//    25-30% faster, at the same instructions), on small ones the latency of an
+//    item's start and the number of items in flight.  One 8-wave workgroup per
+//    CU on 256-column items, its halves a phase apart, was the layout before:
+//    the same time on large batches, but half as many items and workgroups to
+//    fill the chip with, all waves stopping at every item boundary, and its
+//    items fetched one by one from contended counters.  Attention launch,
+//    before -> now: 20 scheduler steps of 1024 tokens (32/8 heads, 604 keys)
+//    538 -> 474 us with their appends; 64 prompts of 300 new tokens, half
+//    cached 210 -> 180 us; 128 prompts of 48 new tokens after 976 shared ones
+//    120 -> 107 us; 199 prompts of 118 tokens (16/2 heads, D 64) 76 -> 40 us.
 //  * the same attention split at a prefix every request of the batch shares
 //    (modes kShared / kSuffix: two launches; kFused: one launch whose items
-//    are 256 columns of the whole batch, over the shared tiles and then each
+//    are 128 columns of the whole batch, over the shared tiles and then each
 //    of their requests' own tiles).
 #include <hip/hip_runtime.h>
 
@@ -51,13 +60,12 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBlock = 16;                    // tokens per pool block
-constexpr int kWaves = 8;                     // waves per attention workgroup
+constexpr int kWaves = 4;                     // waves per attention workgroup (two workgroups per CU)
 constexpr int kThreads = 64 * kWaves;
 constexpr int kColsPerWave = 32;              // query columns per wave (MFMA N)
 constexpr int kCols = kColsPerWave * kWaves;  // query columns per workgroup
 constexpr int kKeys = 64;                     // keys per tile
 constexpr int kTileBlocks = kKeys / kBlock;
-constexpr int kStages = 4;                    // K/V tiles resident in the LDS ring
 constexpr int kMaxGroup = 64;                 // largest Hq / Hkv accepted
 constexpr int kDecodeCols = 32;               // query columns the decode kernel takes per request
 
@@ -82,25 +90,68 @@ __device__ __forceinline__ int k_slot(int m, int c) {
 // 16-byte half (keys 0-7 or 8-15) of V row d of a [D][16] block in LDS.
 __device__ __forceinline__ int v_slot(int d, int hf) { return hf ^ ((d >> 2) & 1) ^ ((d >> 3) & 1); }
 
-// 16 bytes per lane from global memory straight into LDS at lds + 16 * lane
-// (lds wave-uniform).  Issued as inline assembly so that the compiler does
-// not track it: tracked, every LDS read would first wait for all such loads
-// in flight, which defeats the multi-tile prefetch.  Callers wait with an
-// explicit vmcnt.  M0 carries the LDS address; no other code in these
-// kernels uses M0, so it is clobbered without being restored.  Kept out of
-// the kernel templates: an LDS address-space cast instantiated in their
-// host-side pass would drop the launch stubs.
+// One (block, kv head) slab of a pool straight into LDS: instruction i moves
+// 16 bytes per lane from base + off[i] + i KiB (base wave-uniform) to
+// lds + i KiB + 16 * lane; the linear form uses one offset for every
+// instruction.  Issued as inline assembly so that the compiler does not track
+// it: tracked, every LDS read would first wait for all such loads in flight,
+// which defeats the prefetch.  Callers wait with an explicit vmcnt.  M0
+// carries the LDS address; no other code in these kernels uses M0, so it is
+// clobbered without being restored.  The immediate offset moves both
+// addresses, so a slab takes one M0 write, and the scalar base takes no
+// vector address arithmetic.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void global_to_lds16(const void* src, uint8_t* lds) {
-  const uint32_t lds_off = static_cast<uint32_t>(
-      reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint8_t*)lds));
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+__device__ __forceinline__ void load_slab4(uint32_t o0, uint32_t o1, uint32_t o2, uint32_t o3, uint64_t base,
+                                           uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %5\n\ts_nop 0\n\t"
+               "global_load_lds_dwordx4 %0, %4\n\t"
+               "global_load_lds_dwordx4 %1, %4 offset:1024\n\t"
+               "global_load_lds_dwordx4 %2, %4 offset:2048\n\t"
+               "global_load_lds_dwordx4 %3, %4 offset:3072"
                :
-               : "v"(src), "s"(lds_off)
+               : "v"(o0), "v"(o1), "v"(o2), "v"(o3), "s"(base), "s"(lds)
                : "memory", "m0");
 }
+__device__ __forceinline__ void load_slab2(uint32_t o0, uint32_t o1, uint64_t base, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\t"
+               "global_load_lds_dwordx4 %0, %2\n\t"
+               "global_load_lds_dwordx4 %1, %2 offset:1024"
+               :
+               : "v"(o0), "v"(o1), "s"(base), "s"(lds)
+               : "memory", "m0");
+}
+// Kept out of the kernel templates: an LDS address-space cast instantiated in
+// their host-side pass would drop the launch stubs.
+__device__ __forceinline__ uint32_t lds_offset(uint8_t* p) {
+  return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint8_t*)p));
+}
 #pragma clang diagnostic pop
+// Both are wave-uniform; where the compiler cannot tell, this makes them scalar.
+__device__ __forceinline__ uint32_t scalar(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ uint64_t scalar(uint64_t x) {
+  return uint64_t(scalar(uint32_t(x >> 32))) << 32 | scalar(uint32_t(x));
+}
+// A word of a table no kernel writes meanwhile, at a wave-uniform address,
+// through the scalar cache (as a load from constant memory): a vector load
+// would queue behind the tile loads in flight, and its wait would wait for them.
+__device__ __forceinline__ int32_t scalar_load(const int32_t* p) {
+  return *(const __attribute__((address_space(4))) int32_t*)scalar(reinterpret_cast<uint64_t>(p));
+}
+template <int N>
+__device__ __forceinline__ void load_slab(const uint32_t* off, uint64_t base, uint32_t lds) {
+  base = scalar(base);
+  lds = scalar(lds);
+  if constexpr (N == 4) load_slab4(off[0], off[1], off[2], off[3], base, lds);
+  else load_slab2(off[0], off[1], base, lds);
+}
+template <int N>
+__device__ __forceinline__ void load_slab_linear(uint32_t off, uint64_t base, uint32_t lds) {
+  base = scalar(base);
+  lds = scalar(lds);
+  if constexpr (N == 4) load_slab4(off, off, off, off, base, lds);
+  else load_slab2(off, off, base, lds);
+}
 
 // max(x, x of the lane 32 apart): v_permlane32_swap exchanges the two wave halves.
 __device__ __forceinline__ float max_across_halves(float x) {
@@ -164,25 +215,21 @@ __global__ __launch_bounds__(256) void kv_append_kernel(
 // ---------------------------------------------------------------------------
 // paged attention.  Work items are (column tile, kv head, request) triples,
 // numbered request-major with the heaviest column tile of a (request, kv head)
-// first.  The kernel is persistent: one workgroup per CU takes items from
+// first.  The kernel is persistent: two workgroups per CU take items from
 // eight queues, one per XCD, each holding a contiguous range of item numbers
 // so that the items sharing one (request, kv head) -- and so the same K/V
 // blocks -- are worked on under one XCD's L2.  A workgroup drains the queue
 // of its own XCD first, then helps the others.  The queue counters live in
 // the caller's workspace; the last workgroup to finish clears them again.
-//
-// K/V tiles stream through a ring of kStages tiles in LDS, filled straight
-// from HBM by global_load_lds (tile j+2 issued while tile j's softmax runs).
-// Each wave loads one
-// pool block (its K rows and V rows) per tile; the block ids come from the
-// block table through scalar loads, one tile ahead of the load they steer.
 constexpr int kMaxTableBlocks = 1 << 24;  // block-table width accepted (keeps token positions in int)
 // Largest per-lane sum of a tile's exponentials accepted without taking the
 // tile's column max (each exponential is then at most this, 2^8).
 constexpr float kSumLimit = 256.f;
-constexpr int kQueueWords = 16;      // workspace: 8 queue counters, finished workgroups, drained queues
+constexpr int kQueueWords = 16;  // workspace: 8 queue counters, finished workgroups, drained queues
 constexpr int kDoneWord = 8;
 constexpr int kDrainedWord = 9;
+constexpr unsigned kLongRounds = 16;
+constexpr unsigned kNoItem = ~0u, kAsk = ~0u - 1u;
 
 // s_waitcnt vmcnt(n) with the other counters left free (n < 16).
 template <int N>
@@ -203,12 +250,6 @@ __device__ __forceinline__ void bare_barrier() {
   asm volatile("" ::: "memory");
 }
 
-// Index of the XCD (accelerator complex die) running this wave: hardware
-// register XCC_ID (id 20), bits 0-3.
-__device__ __forceinline__ unsigned xcd_id() {
-  return static_cast<unsigned>(__builtin_amdgcn_s_getreg((31 << 11) | 20)) & 7u;
-}
-
 // What one launch of the attention kernel computes.
 //   kFull:   each request's queries over all of its keys (causal).
 //   kShared: first half of a split over a prefix of kv_split keys that every
@@ -221,45 +262,49 @@ __device__ __forceinline__ unsigned xcd_id() {
 // Splitting this way reads the shared K/V once per column tile of the whole
 // batch instead of once per request (the log-sum-exp merge of the two halves
 // is exact up to rounding).
-//   kFused:  the same split in one launch: every item is 256 columns of the
+//   kFused:  the same split in one launch: every item is 128 columns of the
 //            whole batch's packed query rows (like kShared); it runs the
 //            kv_split / 64 tiles every request shares, then, for each
 //            request its rows belong to, that request's own tiles from
-//            kv_split on, masked to that request's columns.  No partial
+//            kv_split on, masked to that request's columns (a wave none of
+//            whose columns belong to the request skips the tile).  No partial
 //            state leaves the workgroup.
 enum AttnMode { kFull = 0, kShared = 1, kSuffix = 2, kFused = 3 };
 
-// kFused: per item, the request tiles after the shared ones, in LDS.
+// kFused: per item, the request tiles after the shared ones, and the requests
+// with rows in the item (at most 128 of them, one per column), in LDS.
 constexpr int kFusedTiles = 2048;
+constexpr int kFusedReqs = kCols + 4;
+
+// Workgroups per CU: at D = 128 the registers hold two waves per SIMD, at
+// D = 64 three.
+constexpr int wgs_per_cu(int D) { return D == 64 ? 3 : 2; }
 
 template <int D, int MODE>
-__global__ __launch_bounds__(kThreads, 1) void paged_attn_kernel(
+__global__ __launch_bounds__(kThreads, wgs_per_cu(D)) void paged_attn_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_pool,
     const uint16_t* __restrict__ v_pool, int num_blocks, const int32_t* __restrict__ block_tables,
     int max_blocks, const int32_t* __restrict__ cu_q, const int32_t* __restrict__ seq_lens, int n_req,
-    int Hq, int Hkv, int n_col_tiles, unsigned n_items, float scale_log2, uint16_t* __restrict__ out,
+    int Hq, int Hkv, int n_col_tiles, unsigned n_items, unsigned chunk, float scale_log2, uint16_t* __restrict__ out,
     unsigned* __restrict__ queue, int kv_split, float* __restrict__ part_o, float* __restrict__ part_ml,
     int part_rows) {
   constexpr int kDch = D / 16;                    // 16-wide contraction chunks of Q.K^T
   constexpr int kDt = D / 32;                     // 32-row output tiles of O^T
   constexpr int kRowBytes = D * 2;                // one K row in LDS
   constexpr int kKch = D / 8;                     // 16-byte chunks per K row
-  constexpr int kKTileBytes = kKeys * kRowBytes;  // one K tile
-  constexpr int kVBlockBytes = D * 32;            // one [D][16] V block
-  constexpr int kVTileBytes = kTileBlocks * kVBlockBytes;
-  constexpr int kStageBytes = kKTileBytes + kVTileBytes;
-  constexpr int kSlabBytes = kBlock * D * 2;      // one (block, kv head) slab in a pool
-  constexpr int kKInsts = kKTileBytes / 1024 / kWaves;  // 1 KB direct loads per wave per tile
-  constexpr int kVInsts = kVTileBytes / 1024 / kWaves;
-  constexpr int kLoads = kKInsts + kVInsts;
-  static_assert(kKInsts >= 1 && kVInsts >= 1 && kWaves == 2 * kTileBlocks, "load split");
-  static_assert(kStages == 4, "ring: two tiles in flight plus two being read");
-  __shared__ __attribute__((aligned(16))) uint8_t ring[kStages * kStageBytes];
-  __shared__ int s_item[2];
-  // kFused: tile T_s + i of an item is tile f_tt[i] of request r_a + f_rel[i],
-  // whose keys at or past f_lim[i] no row of the item sees.
-  constexpr int kFT = MODE == kFused ? kFusedTiles : 1;
-  __shared__ int f_rel[kFT], f_tt[kFT], f_lim[kFT];
+  constexpr int kSlabBytes = kBlock * D * 2;      // one (block, kv head) slab: in a pool, and in LDS
+  constexpr int kTileBytes = kTileBlocks * kSlabBytes;  // one K tile, or one V tile
+  constexpr int kInsts = kSlabBytes / 1024;       // 1 KB direct loads of a slab
+  static_assert(kWaves == kTileBlocks, "each wave loads one pool block of a tile");
+  // Two K tiles, then two V tiles.
+  __shared__ __attribute__((aligned(16))) uint8_t ring[4 * kTileBytes];
+  __shared__ unsigned s_item;
+  // kFused: tile T_s + i of an item is tile f_tile[i] & 0xFFFFFF of the item's
+  // request number f_tile[i] >> 24, which is request f_req[.], whose keys at
+  // or past f_lim[.] no row of the item sees.
+  constexpr bool kIsFused = MODE == kFused;
+  __shared__ uint32_t f_tile[kIsFused ? kFusedTiles : 1];
+  __shared__ int f_req[kIsFused ? kFusedReqs : 1], f_lim[kIsFused ? kFusedReqs : 1];
   __shared__ int f_count;
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -268,211 +313,603 @@ __global__ __launch_bounds__(kThreads, 1) void paged_attn_kernel(
   const int G = Hq / Hkv;
   const size_t slab_stride = size_t(Hkv) * kSlabBytes;
 
-  // Item queues.  Queue x holds items [x*per + min(x, extra), ...) of
-  // per + (x < extra) items; fetch() (lane 0 of wave 0 only) returns the next
-  // item, or -1 once every queue is drained.  The workgroup that takes the
-  // last item of a queue counts it in queue[kDrainedWord]; once the home queue
-  // is drained, that count (one round trip) tells whether any queue still
-  // holds items.  Without it, the walk over the drained queues (one contended
-  // atomic each, about 2 us) sat in front of every workgroup's last item.
-  const unsigned home = xcd_id(), per = n_items >> 3, extra = n_items & 7u;
-  const unsigned nonempty = per > 0 ? 8u : extra;  // queues holding at least one item
-  // With no more items than workgroups (grid = items), workgroup b takes
-  // item b/8 of queue b%8 (the queue of the XCD it is dispatched to in
-  // round-robin order) and nothing else: no queue atomics, no exit count,
-  // and the workspace is left untouched.  Queue x has exactly as many items
-  // as there are such workgroups.
-  unsigned qsel = 0;  // next queue to try, home first (9: the one-item-each mode)
-  auto fetch = [&]() -> int {
+  // Hand-out of the items.  Item numbers are cut into chunks of `chunk`; queue
+  // x (one per XCD) holds the chunks x, x + 8, ..., and is worked by the
+  // workgroups b = x (mod 8), which round-robin dispatch puts on XCD x.
+  //   Short launches (under kLongRounds items a workgroup): the i-th of a
+  // queue's W workgroups first takes items by position: i, 2W-1-i, 2W+i,
+  // 4W-1-i, ... of the queue (turning round so that the heavy-first runs of a
+  // (request, kv head) average out), for three quarters of the rounds; the
+  // rest goes through the queue's counter, which levels uneven items.  The
+  // eight counters share one cache line of the workspace, at 20-25 ns an
+  // atomic for the whole chip: that is why only a quarter of the items pass
+  // through them, and why no workgroup looks at another queue or counts itself
+  // out: each asks its own counter once too often, and the one that gets the
+  // last such number leaves the counter zero for the next call.
+  //   Long launches: everything after the first round goes through the
+  // counters (the XCDs do not run at one speed: leaving each its own eighth
+  // cost 2-3% on 128 prompts of 1984 new tokens, 64/8 heads), and a workgroup
+  // whose queue is drained helps the others.  The workgroup that takes the
+  // last item of a queue counts it in queue[kDrainedWord]; that count (one
+  // round trip) tells whether any queue still holds items, without a walk over
+  // the drained queues.  The last workgroup to finish clears the counters.
+  const unsigned s_x = blockIdx.x & 7u;
+  const bool stealing = n_items >= kLongRounds * gridDim.x;
+  auto queue_wgs = [&](unsigned x) { return (gridDim.x + 7u - x) >> 3; };
+  auto queue_size = [&](unsigned x) {
+    const unsigned nch = (n_items + chunk - 1u) / chunk, mine = (nch + 7u - x) >> 3;
+    return mine * chunk - (((nch - 1u) & 7u) == x ? nch * chunk - n_items : 0u);
+  };
+  auto item_at = [&](unsigned x, unsigned p) { return ((p / chunk) * 8u + x) * chunk + p % chunk; };
+
+  // This wave's direct loads of a tile: pool block `wave` of the tile, i.e.
+  // its own quarter of a K tile and of a V tile.  LDS slot (row m, slot p) of
+  // a K tile holds chunk k_slot(m, p) of key key_row(m); slot (d, p) of a V
+  // block holds half v_slot(d, p) of row d.  Instruction i of a slab carries
+  // an immediate offset of i KiB that moves its source and its destination
+  // alike; koff takes the source's share back out (+1 KiB so that it stays
+  // positive: the base passed is 1 KiB lower).  The V source moves by exactly
+  // that, so one offset serves all its instructions.
+  uint32_t koff[kInsts];
+#pragma unroll
+  for (int i = 0; i < kInsts; ++i) {
+    const int m = i * (1024 / kRowBytes) + lane / kKch;
+    koff[i] = uint32_t(key_row(m) * kRowBytes + k_slot<D>(m, lane % kKch) * 16 + 1024 - i * 1024);
+  }
+  const uint32_t voff = uint32_t((lane >> 1) * 32 + v_slot(lane >> 1, lane & 1) * 16);
+  const uint32_t ring0 = lds_offset(ring) + wave * kSlabBytes;  // this wave's quarter of K tile 0
+
+  // By position: this workgroup's next place in its queue, the end of that
+  // part, the step to the place after; then what is left for the counter.
+  const unsigned s_wgs = queue_wgs(s_x), s_size = queue_size(s_x);
+  const unsigned s_rounds = s_size / s_wgs;
+  const unsigned s_end =
+      s_rounds <= 1u ? min(s_size, s_wgs) : stealing ? s_wgs : (s_rounds - s_rounds / 4u) * s_wgs;
+  const unsigned s_left = s_size - s_end;
+  unsigned s_next = blockIdx.x >> 3, s_step = 2u * s_wgs - 1u - 2u * (blockIdx.x >> 3);
+  // The item to start next; kAsk: it is to be asked for.
+  auto next_static = [&]() -> unsigned {
+    const unsigned at = s_next;
+    s_next += s_step;
+    s_step = 2u * s_wgs - s_step;
+    return at < s_end ? item_at(s_x, at) : (s_left ? kAsk : kNoItem);
+  };
+  // Lane 0 of wave 0 only: asks a counter; the item behind its answer.
+  unsigned qsel = 0;  // (stealing) next queue to try, home first
+  auto take = [&]() {
+    return __hip_atomic_fetch_add(queue + ((s_x + qsel) & 7u), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  auto resolve = [&](unsigned i) -> unsigned {
+    if (!stealing) {
+      if (i < s_left) return item_at(s_x, s_end + i);
+      if (i == s_left + s_wgs - 1u) __hip_atomic_store(queue + s_x, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return kNoItem;
+    }
     while (qsel < 8u) {
-      const unsigned x = (home + qsel) & 7u;
-      const unsigned size = per + (x < extra ? 1u : 0u), base = x * per + min(x, extra);
-      const unsigned i = __hip_atomic_fetch_add(queue + x, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (i + 1 == size) __hip_atomic_fetch_add(queue + kDrainedWord, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (i < size) return int(base + i);
+      const unsigned x = (s_x + qsel) & 7u, first = queue_wgs(x), left = queue_size(x) - first;
+      if (i + 1 == left) __hip_atomic_fetch_add(queue + kDrainedWord, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (i < left) return item_at(x, first + i);
       ++qsel;
       if (qsel == 1u &&
-          __hip_atomic_load(queue + kDrainedWord, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= nonempty)
+          __hip_atomic_load(queue + kDrainedWord, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= 8u)
         qsel = 8u;
+      if (qsel < 8u) i = take();
     }
-    return -1;
+    return kNoItem;
+  };
+  unsigned w = next_static();
+
+  // Columns are split into (query row, head of the group) by a 16-bit
+  // reciprocal of G: exact for the offsets met here, below G + 128 <= 192
+  // (u * (65536 / G + 1 - 65536 / G exactly) < u * G / 65536 < 1 / G).
+  const unsigned recip = 65536u / unsigned(G) + 1u;
+  auto div_g = [&](int u) { return int((unsigned(u) * recip) >> 16); };
+
+  // State of the item whose loads were last started ...
+  int kvh = 0, row0 = 0, rem0 = 0;  // kv head; query row and head of its first column
+  int n_valid = 0;                  // its query columns (up to 128)
+  int n_tiles = 0, key_lim = 0, n_blk_used = 0, wave_last = -1, wave_pos_min = 0, t0 = 0;
+  int pos = 0, my_ord = 0, my_pos = 0;  // of this lane's column
+  bool wave_active = false;
+  const int32_t* bt = block_tables;
+  int id_next = 0, raw_next = 0;  // block id of the next tile to issue V of, raw id of the one after
+  const int T_s = kv_split / kKeys;  // kFused: tiles every request shares (at least 3)
+  const uint64_t kbase0 = reinterpret_cast<uint64_t>(k_pool) - 1024, vbase0 = reinterpret_cast<uint64_t>(v_pool);
+  // The two K and the two V buffers alternate by a tile count that runs on
+  // across items, so that the first loads of an item never land in the V tile
+  // a slower wave of the previous item still reads.
+  int tbase = 0;
+  bf16x8 qf[kDch];           // Q operand of this wave's 32 columns
+  f32x16 o[kDt];             // unnormalised O^T
+  float m_used = -INFINITY;  // max (log2 units) the exponentials of this column are taken against
+  float l_run = 0.f;         // this lane half's share of the column's exponential sum
+  bf16x8 pb[kTileBlocks];    // P of the tile whose V^T P^T is still due
+  f32x16 sc0, sc1;           // scores of the tile whose softmax is next
+  // Defined here, as whatever the registers hold (an undefined value would be
+  // carried in registers of its own, 48 of them across the tile loop).
+  asm volatile("" : "=v"(sc0), "=v"(sc1), "=v"(pb[0]), "=v"(pb[1]), "=v"(pb[2]), "=v"(pb[3]));
+#pragma unroll
+  for (int i = 0; i < kDch; ++i) asm volatile("" : "=v"(qf[i]));
+#pragma unroll
+  for (int i = 0; i < kDt; ++i) asm volatile("" : "=v"(o[i]));
+
+  auto raw_id = [&](int tl) { return scalar_load(bt + min((t0 + tl) * kTileBlocks + wave, max_blocks - 1)); };
+  // Pool block of this wave in tile tl, from the raw table entry; unusable
+  // ids read block 0 instead (stray K rows only meet masked scores, stray V
+  // rows past key_lim are zeroed below).
+  auto usable = [&](int tl, int id) {
+    if constexpr (kIsFused) return (id >= 0 && id < num_blocks) ? id : 0;
+    return ((t0 + tl) * kTileBlocks + wave < n_blk_used && id >= 0 && id < num_blocks) ? id : 0;
+  };
+  auto buf = [&](int tl) { return (unsigned(tbase + tl) & 1u) * kTileBytes; };
+  auto slab_at = [&](int id) { return size_t(id) * slab_stride + size_t(kvh) * kSlabBytes; };
+  auto issue_k = [&](int tl, int id) { load_slab<kInsts>(koff, kbase0 + slab_at(id), ring0 + buf(tl)); };
+  auto issue_v = [&](int tl, int id) {
+    load_slab_linear<kInsts>(voff, vbase0 + slab_at(id), ring0 + 2 * kTileBytes + buf(tl));
+  };
+  auto k_at = [&](int tl) { return ring + buf(tl); };
+  auto v_at = [&](int tl) { return ring + 2 * kTileBytes + buf(tl); };
+  // Element offset in q / out of the row of column offset co of an item.
+  auto row_of = [&](int r0, int m0, int h, int co) {
+    const int u = m0 + co, t = div_g(u);
+    return (size_t(r0 + t) * Hq + size_t(h) * G + (u - t * G)) * D;
   };
 
-  // This wave's direct loads of a tile: all from pool block wave/2 of the tile.
-  // LDS slot (row m, slot p) of a K tile holds chunk k_slot(m, p) of key
-  // key_row(m); slot (d, p) of a V block holds half v_slot(d, p) of row d.
-  uint32_t koff[kKInsts], voff[kVInsts];
-#pragma unroll
-  for (int i = 0; i < kKInsts; ++i) {
-    const int g = wave * kKInsts + i;
-    const int m = g * (1024 / kRowBytes) + lane / kKch;
-    koff[i] = uint32_t((key_row(m) & 15) * kRowBytes + k_slot<D>(m, lane % kKch) * 16);
-  }
-#pragma unroll
-  for (int i = 0; i < kVInsts; ++i) {
-    const int g = wave * kVInsts + i;
-    const int d = (g * 1024 % kVBlockBytes) / 32 + (lane >> 1);
-    voff[i] = uint32_t(d * 32 + v_slot(d, lane & 1) * 16);
-  }
-  const int my_blk = wave >> 1;
-  const bool lag = wave >= kWaves / 2;
-
-  if (tid == 0) {
-    if (n_items <= gridDim.x) {
-      const unsigned x = blockIdx.x & 7u;
-      s_item[0] = int(x * per + min(x, extra) + (blockIdx.x >> 3));
-      qsel = 9u;  // later fetches return -1
-    } else {
-      s_item[0] = fetch();
-    }
-    wait_lgkmcnt0();
-  }
-  __syncthreads();
-
-  // Ring stages are numbered by a tile count running across items, so the
-  // first tiles of an item never land in the stage the previous item still
-  // reads.
-  int tbase = 0;
-  for (int it = 0;; ++it) {
-    const int w = __builtin_amdgcn_readfirstlane(s_item[it & 1]);
-    if (w < 0) break;
+  // Starts item w: reads its lengths and first block ids, issues the loads of
+  // its K tiles 0 and 1, V tile 0 and Q.  False, with nothing issued, if the
+  // item holds no query columns.
+  auto start_item = [&]() -> bool {
+    w = __builtin_amdgcn_readfirstlane(w);
     // kFused numbers items kv-head-major (the items of one kv head share the
     // prefix blocks, under one XCD's L2).
-    const int tile = MODE == kFused ? int(unsigned(w) % unsigned(n_col_tiles))
-                                    : n_col_tiles - 1 - int(unsigned(w) % unsigned(n_col_tiles));
-    const unsigned rest = unsigned(w) / unsigned(n_col_tiles);
-    const int kvh = MODE == kFused ? int(rest) : int(rest % unsigned(Hkv));
-    const int r = MODE == kShared || MODE == kFused ? 0 : int(rest / unsigned(Hkv));
+    const int tile = kIsFused ? int(w % unsigned(n_col_tiles)) : n_col_tiles - 1 - int(w % unsigned(n_col_tiles));
+    const unsigned rest = w / unsigned(n_col_tiles);
+    kvh = kIsFused ? int(rest) : int(rest % unsigned(Hkv));
+    const int r = MODE == kShared || kIsFused ? 0 : int(rest / unsigned(Hkv));
     // First key tile of this launch (the suffix half starts at kv_split).
-    const int t0 = MODE == kSuffix ? kv_split / kKeys : 0;
+    t0 = MODE == kSuffix ? kv_split / kKeys : 0;
     // This item's lengths and the block ids of its first three tiles are
     // loaded together: one round trip for all.  A block id is loaded
     // unconditionally (clamped into the table row) and checked where it is
     // used, so that no wait follows the scalar load.
-    const int32_t* bt = block_tables + size_t(r) * max_blocks;
-    auto raw_id = [&](int tl) { return bt[min((t0 + tl) * kTileBlocks + my_blk, max_blocks - 1)]; };
-    // kFused: request (relative to r_a) and tile of item tile tl.
-    auto fused_src = [&](int tl, int& rel, int& tt) {
-      if (tl < kv_split / kKeys) {
-        rel = 0;
-        tt = tl;
-      } else {
-        rel = __builtin_amdgcn_readfirstlane(f_rel[tl - kv_split / kKeys]);
-        tt = __builtin_amdgcn_readfirstlane(f_tt[tl - kv_split / kKeys]);
-      }
-    };
+    bt = block_tables + size_t(r) * max_blocks;
     // The shared half treats the whole batch as one request whose queries all
     // follow the kv_split shared keys.
-    const int q0 = MODE == kShared || MODE == kFused ? 0 : cu_q[r];
-    const int q_end = MODE == kShared || MODE == kFused ? cu_q[n_req] : cu_q[r + 1];
-    const int L_in = MODE == kShared || MODE == kFused ? kv_split + (q_end - q0) : seq_lens[r];
+    const int q0 = MODE == kShared || kIsFused ? 0 : scalar_load(cu_q + r);
+    const int q_end = scalar_load(MODE == kShared || kIsFused ? cu_q + n_req : cu_q + r + 1);
+    const int L_in = MODE == kShared || kIsFused ? kv_split + (q_end - q0) : scalar_load(seq_lens + r);
     const int raw_id0 = raw_id(0), raw_id1 = raw_id(1);
-    int raw_next = raw_id(2);  // raw id of the next tile to issue after tile 1
+    raw_next = raw_id(2);
     // First use of all six values at once: the loads are issued together and
     // waited for once.
     asm volatile("" : : "s"(q0), "s"(q_end), "s"(L_in), "s"(raw_id0), "s"(raw_id1), "s"(raw_next));
     // In the split modes, rows past the partial-state buffer are not computed.
-    const int q_len = MODE == kFull || MODE == kFused ? q_end - q0 : min(q_end, part_rows) - q0;
+    const int q_len = MODE == kFull || kIsFused ? q_end - q0 : min(q_end, part_rows) - q0;
     const int n_cols = q_len * G;
     const int col0 = tile * kCols;
-    const int L = MODE == kShared || MODE == kFused ? L_in : min(L_in, max_blocks * kBlock);
-    if (q_len <= 0 || col0 >= n_cols || q_len > L) {  // nothing to do for this item
-      if (tid == 0) {
-        s_item[(it + 1) & 1] = fetch();
-        wait_lgkmcnt0();
-      }
-      __syncthreads();
-      continue;
-    }
+    const int L = MODE == kShared || kIsFused ? L_in : min(L_in, max_blocks * kBlock);
+    if (q_len <= 0 || col0 >= n_cols || q_len > L) return false;
     const int qstart = L - q_len;  // position of the request's first query
-
-    const int T_s = kv_split / kKeys;  // kFused: tiles every request shares (at least 3)
-    int r_a = 0, my_rel = 0, my_pos = 0;
+    const int row_a = col0 / G;
+    row0 = q0 + row_a;
+    rem0 = col0 - row_a * G;
+    n_valid = min(n_cols - col0, kCols);
+    const int wave_first = wave * kColsPerWave;
+    wave_active = wave_first < n_valid;
     // This lane's query column (padding columns repeat the last valid one).
-    const int col = col0 + wave * kColsPerWave + n;
-    const bool col_valid = col < n_cols;
-    const int colc = col_valid ? col : n_cols - 1;
-    const int t = colc / G;
-    const int pos = qstart + t;
-    const size_t qrow = (size_t(q0 + t) * Hq + size_t(kvh) * G + (colc - t * G)) * D;
-
-    const int wave_first = col0 + wave * kColsPerWave;
-    const bool wave_active = wave_first < n_cols;
-    const int wave_pos_min = qstart + min(wave_first, n_cols - 1) / G;
-    const int wg_pos_max = qstart + min(col0 + kCols - 1, n_cols - 1) / G;
+    const int co = min(wave_first + n, n_valid - 1);
+    const int pos0 = qstart + row_a;
+    pos = MODE == kShared ? kv_split - 1 : pos0 + div_g(rem0 + co);
+    wave_pos_min = MODE == kShared ? kv_split - 1 : pos0 + div_g(rem0 + min(wave_first, n_valid - 1));
+    const int wg_pos_max = pos0 + div_g(rem0 + n_valid - 1);
     // Keys at or past key_lim are masked everywhere (and their V rows zeroed).
-    const int key_lim = MODE == kShared ? kv_split : wg_pos_max + 1;
+    key_lim = MODE == kShared ? kv_split : wg_pos_max + 1;
     // Tiles of this launch (kFused: the shared ones until the item's list is
-    // read after the first barrier).
-    int n_tiles = MODE == kFused ? T_s : (key_lim - 1) / kKeys + 1 - t0;
-    const int n_blk_used = (key_lim + kBlock - 1) / kBlock;  // <= ceil(L / 16) <= max_blocks
+    // read after the next barrier).
+    // (at least one, also where the caller's shared_len breaks its contract)
+    n_tiles = kIsFused ? T_s : max((key_lim - 1) / kKeys + 1 - t0, 1);
+    n_blk_used = (key_lim + kBlock - 1) / kBlock;  // <= ceil(L / 16) <= max_blocks
     // Last tile (counted from t0) holding a key some column of this wave sees
     // (-1: no column).
-    int wave_last =
-        !wave_active ? -1
-        : MODE == kShared || MODE == kFused ? n_tiles - 1
-                          : (qstart + min(wave_first + kColsPerWave - 1, n_cols - 1) / G) / kKeys - t0;
-
-    bf16x8 qf[kDch];
+    wave_last = !wave_active ? -1
+                : MODE == kShared
+                    ? n_tiles - 1
+                    : (pos0 + div_g(rem0 + min(wave_first + kColsPerWave, n_valid) - 1)) / kKeys - t0;
+    const int id0 = usable(0, raw_id0);
+    id_next = usable(1, raw_id1);
+    issue_k(0, id0);
+    issue_v(0, id0);
+    if (1 < n_tiles) issue_k(1, id_next);
+    const size_t qrow = row_of(row0, rem0, kvh, co);
 #pragma unroll
     for (int kc = 0; kc < kDch; ++kc) qf[kc] = as_bf16x8(*(const u32x4*)(q + qrow + kc * 16 + hh * 8));
-    // kFused: block id of this wave in item tile tl (shared tiles from any
-    // request's table, request tiles from the owner's).
-    auto fused_raw = [&](int tl) {
-      int rel, tt;
-      fused_src(tl, rel, tt);
-      return block_tables[size_t(r_a + rel) * max_blocks + min(tt * kTileBlocks + my_blk, max_blocks - 1)];
-    };
-
-
-    const uint8_t* kbase = reinterpret_cast<const uint8_t*>(k_pool) + size_t(kvh) * kSlabBytes;
-    const uint8_t* vbase = reinterpret_cast<const uint8_t*>(v_pool) + size_t(kvh) * kSlabBytes;
-    // Pool block of this wave in tile tl, from the raw table entry; unusable
-    // ids read block 0 instead (stray K rows only meet masked scores, stray V
-    // rows past key_lim are zeroed below).
-    auto usable = [&](int tl, int id) {
-      if constexpr (MODE == kFused) return (id >= 0 && id < num_blocks) ? id : 0;
-      return ((t0 + tl) * kTileBlocks + my_blk < n_blk_used && id >= 0 && id < num_blocks) ? id : 0;
-    };
-    auto stage = [&](int tl) { return ring + (unsigned(tbase + tl) % unsigned(kStages)) * kStageBytes; };
-    auto issue_tile = [&](int tl, int raw) {
-      const int id = usable(tl, raw);
-      uint8_t* st = stage(tl);
-      const uint8_t* ksrc = kbase + size_t(id) * slab_stride;
-      const uint8_t* vsrc = vbase + size_t(id) * slab_stride;
+    // kFused: with the first tiles and Q in flight, find the requests of the
+    // item's rows, this lane's request and position, and (wave 0) the list of
+    // request tiles; tiles 0-2 are shared, so request 0's table gave their ids.
+    // Scalar loads only: they do not queue behind the tiles' vector loads.
+    if constexpr (kIsFused) {
+      const int row_b = row_a + div_g(rem0 + n_valid - 1);
+      // lo: the largest request whose first row is at or before row_a; seven
+      // probes a round trip
+      int lo = 0, hi = n_req;  // cu_q[lo] <= row_a < cu_q[hi]
+      while (hi - lo > 1) {
+        const int st = (hi - lo + 7) >> 3;
+        int c[7], next = lo;
 #pragma unroll
-      for (int i = 0; i < kKInsts; ++i) global_to_lds16(ksrc + koff[i], st + (wave * kKInsts + i) * 1024);
+        for (int k = 0; k < 7; ++k) c[k] = scalar_load(cu_q + min(lo + st * (k + 1), hi));
 #pragma unroll
-      for (int i = 0; i < kVInsts; ++i)
-        global_to_lds16(vsrc + voff[i], st + kKTileBytes + (wave * kVInsts + i) * 1024);
-    };
-    // Zero the V rows of keys >= key_lim in a V tile (only the tile crossing it).
-    auto zero_v_tail = [&](int j0, uint8_t* sV, int key_lim) {
-      for (int slot = tid; slot < kVTileBytes / 16; slot += kThreads) {
-        const int kb = slot / (2 * D), d = (slot % (2 * D)) >> 1, p = slot & 1;
-        const int nvalid = key_lim - (j0 + kb * kBlock + v_slot(d, p) * 8);
-        if (nvalid < 8) {
-          u32x4* ptr = (u32x4*)(sV + kb * kVBlockBytes + d * 32 + p * 16);
-          u32x4 v = *ptr;
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            v[e] &= (2 * e < nvalid ? 0x0000FFFFu : 0u) | (2 * e + 1 < nvalid ? 0xFFFF0000u : 0u);
-          *ptr = v;
+        for (int k = 0; k < 7; ++k)
+          if (lo + st * (k + 1) < hi && c[k] <= row_a) next = lo + st * (k + 1);
+        hi = min(next + st, hi);
+        lo = next;
+      }
+      const int row_l = row_a + div_g(rem0 + co);
+      int n_list = 0, ord = 0;
+      my_ord = 0;
+      my_pos = 0;
+      // requests lo, lo + 1, ... while their rows start at or before row_b
+      for (int rr = lo; rr < n_req && ord < kFusedReqs; ++rr) {
+        const int b0 = scalar_load(cu_q + rr);
+        if (b0 > row_b) break;
+        const int b1 = scalar_load(cu_q + rr + 1);
+        const int lo_row = max(b0, row_a), hi_row = min(b1 - 1, row_b);
+        if (lo_row > hi_row) continue;  // no row of this item (or an empty request)
+        const int Lr = min(scalar_load(seq_lens + rr), max_blocks * kBlock);
+        if (row_l >= b0 && row_l < b1) {
+          my_ord = ord;
+          my_pos = Lr - (b1 - b0) + (row_l - b0);
         }
+        // keys the item's rows of rr see end at lim; its tiles T_s .. go to the list
+        const int lim = Lr - (b1 - b0) + (hi_row - b0) + 1;
+        const int cnt = min(max(0, (lim + kKeys - 1) / kKeys - T_s), kFusedTiles - n_list);
+        if (wave == 0) {
+          for (int k = lane; k < cnt; k += 64) f_tile[n_list + k] = uint32_t(ord) << 24 | uint32_t(T_s + k);
+          if (lane == 0) {
+            f_req[ord] = rr;
+            f_lim[ord] = lim;
+          }
+        }
+        n_list += cnt;
+        ++ord;
+      }
+      if (wave == 0) {
+        if (lane == 0) f_count = n_list;
+        wait_lgkmcnt0();  // the list is in LDS before the next barrier
+      }
+    }
+    return true;
+  };
+
+  // Zero the V rows of keys >= lim in this wave's pool block of a V tile
+  // starting at key j0 (the wave's own loads of it have landed; the other
+  // waves read it only after the next barrier).
+  auto zero_v_tail = [&](int tl, int j0, int lim) {
+    const int nv_blk = lim - (j0 + wave * kBlock);
+    if (nv_blk >= kBlock) return;
+    uint8_t* sV = v_at(tl) + wave * kSlabBytes;
+    const int nvalid = nv_blk - v_slot(lane >> 1, lane & 1) * 8;
+#pragma unroll
+    for (int i = 0; i < kInsts; ++i) {
+      u32x4* ptr = (u32x4*)(sV + i * 1024 + lane * 16);
+      u32x4 v = *ptr;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        v[e] &= (2 * e < nvalid ? 0x0000FFFFu : 0u) | (2 * e + 1 < nvalid ? 0xFFFF0000u : 0u);
+      *ptr = v;
+    }
+    wait_lgkmcnt0();
+  };
+
+  // Masks of the score tile starting at key j0 (scores of keys a column does
+  // not see become -inf).  Lane half hh holds keys j0 + (e>>3)*16 + 8*hh +
+  // (e&7) [+32] of the tile.
+  auto mask = [&](int j0, int fused_thr) __attribute__((always_inline)) {
+    auto keep_upto = [&](int rel) __attribute__((always_inline)) {  // key (e>>3)*16 + (e&7) [+32] is visible iff <= rel
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int k = (e >> 3) * 16 + (e & 7);
+        sc0[e] = k > rel ? -INFINITY : sc0[e];
+        sc1[e] = k + 32 > rel ? -INFINITY : sc1[e];
       }
     };
+    if (kIsFused && fused_thr != INT_MAX) keep_upto(fused_thr);  // a request tile: its own rows, causal
+    if (!kIsFused && j0 + kKeys - 1 > wave_pos_min) keep_upto(pos - j0 - hh * 8);  // causal (kShared: pos is its last key)
+    if (MODE == kSuffix && j0 < kv_split) {  // keys of the shared prefix: done before
+      int lo = kv_split - j0 - hh * 8;
+      asm volatile("" : "+v"(lo));  // as above
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int k = (e >> 3) * 16 + (e & 7);
+        sc0[e] = k < lo ? -INFINITY : sc0[e];
+        sc1[e] = k + 32 < lo ? -INFINITY : sc1[e];
+      }
+    }
+  };
 
-    f32x16 o[kDt];
+  // Softmax step of a masked score tile: P = exp2(S * scale_log2 - m_used),
+  // rounded to bf16 for the V^T P^T product while the row sum adds the fp32
+  // values.  m_used is the column max the exponentials were last rescaled to.
+  // The step is accepted as long as every lane's sum of its exponentials lies
+  // in [0, 2^8] (so no single one exceeds 2^8, the headroom the fp32
+  // accumulators are given); otherwise -- on the first tile (`first`: m_used
+  // is still -inf), or when the max has grown -- the tile's column max is
+  // taken, O and the sum are rescaled to it and the exponentials recomputed.
+  auto softmax = [&](bool first) __attribute__((always_inline)) {
+    // Exponentials against the running max m_used, summed per lane half.
+    auto exps = [&](float* ls) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(sc0[e], scale_log2, -m_used));
+        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(sc1[e], scale_log2, -m_used));
+        pb[e >> 3][e & 7] = (__bf16)p0;
+        pb[2 + (e >> 3)][e & 7] = (__bf16)p1;
+        ls[e & 3] = e < 4 ? p0 + p1 : ls[e & 3] + (p0 + p1);
+      }
+      // The bf16 operands are formed here, not after the acceptance test:
+      // sunk past it, all 32 fp32 exponentials would stay live across it.
+      asm volatile("" : "+v"(pb[0]), "+v"(pb[1]), "+v"(pb[2]), "+v"(pb[3]));
+    };
+    float ls[4];
+    float tsum = 0.f;
+    bool slow = first;
+    if (!first) {
+      exps(ls);
+      tsum = (ls[0] + ls[1]) + (ls[2] + ls[3]);
+      // Accepted unless some lane's sum exceeds kSumLimit or is not a
+      // number (an overflow, or -inf - -inf).
+      slow = __ballot(!(tsum <= kSumLimit)) != 0;
+    }
+    if (slow) {
+      float mx, mx2;
+      asm("v_max3_f32 %0, %1, %2, %3\n\t"
+          "v_max3_f32 %0, %0, %4, %5\n\t"
+          "v_max3_f32 %0, %0, %6, %7\n\t"
+          "v_max3_f32 %0, %0, %8, %9\n\t"
+          "v_max3_f32 %0, %0, %10, %11\n\t"
+          "v_max3_f32 %0, %0, %12, %13\n\t"
+          "v_max3_f32 %0, %0, %14, %15\n\t"
+          "v_max3_f32 %0, %0, %16, %17"
+          : "=&v"(mx)
+          : "v"(sc0[0]), "v"(sc1[0]), "v"(sc0[1]), "v"(sc1[1]), "v"(sc0[2]), "v"(sc1[2]), "v"(sc0[3]),
+            "v"(sc1[3]), "v"(sc0[4]), "v"(sc1[4]), "v"(sc0[5]), "v"(sc1[5]), "v"(sc0[6]), "v"(sc1[6]),
+            "v"(sc0[7]), "v"(sc1[7]), "v"(sc0[8]));
+      asm("v_max3_f32 %0, %1, %2, %3\n\t"
+          "v_max3_f32 %0, %0, %4, %5\n\t"
+          "v_max3_f32 %0, %0, %6, %7\n\t"
+          "v_max3_f32 %0, %0, %8, %9\n\t"
+          "v_max3_f32 %0, %0, %10, %11\n\t"
+          "v_max3_f32 %0, %0, %12, %13\n\t"
+          "v_max3_f32 %0, %0, %14, %15\n\t"
+          "v_max3_f32 %0, %0, %16, %0"
+          : "=&v"(mx2)
+          : "v"(mx), "v"(sc1[8]), "v"(sc0[9]), "v"(sc1[9]), "v"(sc0[10]), "v"(sc1[10]), "v"(sc0[11]),
+            "v"(sc1[11]), "v"(sc0[12]), "v"(sc1[12]), "v"(sc0[13]), "v"(sc1[13]), "v"(sc0[14]),
+            "v"(sc1[14]), "v"(sc0[15]), "v"(sc1[15]));
+      mx = mx2;
+      mx = max_across_halves(mx) * scale_log2;
+      const float m_new = fmaxf(m_used, mx);
+      const float alpha = __builtin_amdgcn_exp2f(m_used - m_new);
+      m_used = m_new;
+      l_run *= alpha;
+#pragma unroll
+      for (int dt = 0; dt < kDt; ++dt)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) o[dt][e] *= alpha;
+      exps(ls);
+      tsum = (ls[0] + ls[1]) + (ls[2] + ls[3]);
+    }
+    l_run += tsum;
+  };
+
+  // One matrix-core phase: O += V(sV) P over the tile's pool blocks
+  // (kTileBlocks * kDt products), then S = K(sK) Q^T (2 * kDch products),
+  // as one software-pipelined stream whose LDS operands are read kPrefetch
+  // products ahead, so that a lone wave keeps the matrix core busy.
+  constexpr int kPvSteps = kTileBlocks * kDt, kQkSteps = 2 * kDch, kPrefetch = 6;
+  auto m_phase = [&](auto with_pv, auto with_qk, const uint8_t* sV, const uint8_t* sK) {
+    constexpr int first = decltype(with_pv)::value ? 0 : kPvSteps;
+    constexpr int last = decltype(with_qk)::value ? kPvSteps + kQkSteps : kPvSteps;
+    auto operand = [&](int st) -> bf16x8 {
+      if (st < kPvSteps) {
+        const int b = st / kDt, d = (st % kDt) * 32 + n;
+        return *(const bf16x8*)(sV + b * kSlabBytes + d * 32 + (v_slot(d, hh) << 4));
+      }
+      const int u = st - kPvSteps, m = (u & 1) * 32 + n;
+      return *(const bf16x8*)(sK + m * kRowBytes + (k_slot<D>(m, (u >> 1) * 2 + hh) << 4));
+    };
+    // Raised issue priority for the phase: when another wave's softmax and
+    // this wave's next product are both ready, the product goes first, so
+    // the matrix core does not wait behind a run of vector instructions.
+    // The scheduling barriers keep the phase's instructions between the two
+    // priority changes.
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (decltype(with_qk)::value) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) { sc0[e] = 0.f; sc1[e] = 0.f; }
+    }
+    bf16x8 buf[kPrefetch];
+#pragma unroll
+    for (int st = first; st < first + kPrefetch && st < last; ++st) buf[st % kPrefetch] = operand(st);
+#pragma unroll
+    for (int st = first; st < last; ++st) {
+      const bf16x8 a = buf[st % kPrefetch];
+      if (st + kPrefetch < last) buf[st % kPrefetch] = operand(st + kPrefetch);
+      if (st < kPvSteps) {
+        const int dt = st % kDt;
+        o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb[st / kDt], o[dt], 0, 0, 0);
+      } else {
+        const int u = st - kPvSteps;
+        if (u & 1) sc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[u >> 1], sc1, 0, 0, 0);
+        else sc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[u >> 1], sc0, 0, 0, 0);
+      }
+    }
+    // Pin the pipelined order for the scheduler (mask 0x100: LDS reads,
+    // 0x008: matrix-core ops): kPrefetch reads, then one product per read,
+    // then the last kPrefetch products.
+    constexpr int steps = last - first, lead = steps < kPrefetch ? steps : kPrefetch;
+    __builtin_amdgcn_sched_group_barrier(0x100, lead, 0);
+#pragma unroll
+    for (int st = 0; st < steps - lead; ++st) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, lead, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  using yes = std::true_type;
+  using no = std::false_type;
+
+  // Stores O of a finished item (its row0, rem0, kvh, n_valid as p_*), through
+  // this wave's 4 KiB of LDS at tb.
+  auto store_item = [&](int p_row0, int p_rem0, int p_kvh, int p_valid, uint8_t* tb) {
+    if (wave * kColsPerWave >= p_valid) return;
+    const float l_tot = l_run + __shfl_xor(l_run, 32);
+    if constexpr (MODE == kShared) {  // unnormalised O, max and sum for the suffix half
+      const int co = wave * kColsPerWave + n;
+      if (co < p_valid) {
+        const size_t prow = row_of(p_row0, p_rem0, p_kvh, co) / D;
+        if (hh == 0) {
+          part_ml[prow * 2] = m_used;
+          part_ml[prow * 2 + 1] = l_tot;
+        }
+#pragma unroll
+        for (int dt = 0; dt < kDt; ++dt)
+#pragma unroll
+          for (int g4 = 0; g4 < 4; ++g4) {
+            const f32x4 v = {o[dt][g4 * 4], o[dt][g4 * 4 + 1], o[dt][g4 * 4 + 2], o[dt][g4 * 4 + 3]};
+            *(f32x4*)(part_o + prow * D + dt * 32 + g4 * 8 + hh * 4) = v;
+          }
+      }
+    } else if constexpr (D == 128) {
+      // The normalised O leaves through LDS.  In the matrix-core layout a
+      // lane holds 8-byte pieces of one output row, so direct stores put 16
+      // bytes of 32 different rows into every instruction.  Each wave
+      // writes its 32 rows, 64 dimensions at a time, then stores whole
+      // 128-byte half rows, 8 lanes per half row.  16-byte chunks are
+      // XOR-swizzled by row against bank conflicts.
+      const float inv = 1.f / l_tot;
+      static_assert(kSlabBytes >= kColsPerWave * 128, "transpose area");
+      size_t orow4[4];  // output row of the 4 rows this lane stores
+      bool ok4[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int co = wave * kColsPerWave + r * 8 + (lane >> 3);
+        ok4[r] = co < p_valid;
+        orow4[r] = row_of(p_row0, p_rem0, p_kvh, co);
+      }
+      const int ch_r = lane & 7;
+#pragma unroll
+      for (int p = 0; p < kDt / 2; ++p) {
+#pragma unroll
+        for (int dl = 0; dl < 2; ++dl)
+#pragma unroll
+          for (int g4 = 0; g4 < 4; ++g4) {
+            bf16x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = (__bf16)(o[2 * p + dl][g4 * 4 + e] * inv);
+            const int ch = dl * 4 + g4;
+            *(bf16x4*)(tb + n * 128 + ((ch ^ (n & 7)) << 4) + hh * 8) = v;
+          }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = r * 8 + (lane >> 3);
+          const u32x4 val = *(const u32x4*)(tb + row * 128 + ((ch_r ^ (row & 7)) << 4));
+          if (ok4[r]) *(u32x4*)(out + orow4[r] + p * 64 + ch_r * 8) = val;
+        }
+      }
+    } else {
+      const float inv = 1.f / l_tot;
+      const int co = wave * kColsPerWave + n;
+      if (co < p_valid) {
+        uint16_t* orow = out + row_of(p_row0, p_rem0, p_kvh, co);
+#pragma unroll
+        for (int dt = 0; dt < kDt; ++dt)
+#pragma unroll
+          for (int g4 = 0; g4 < 4; ++g4) {
+            bf16x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = (__bf16)(o[dt][g4 * 4 + e] * inv);
+            *(bf16x4*)(orow + dt * 32 + g4 * 8 + hh * 4) = v;
+          }
+      }
+    }
+  };
+
+  // Schedule of an item; every wave runs
+  //   start:  issue K(0), V(0), K(1) and Q
+  //   wait for them; barrier S
+  //   M_0 = [S(0) = K(0) Q^T]
+  //   then for every tile j:
+  //     wait for this wave's own loads (K(j+1), V(j)); barrier B_j;
+  //     issue K(j+2) and V(j+1);
+  //     V_j = [softmax S(j) -> P(j)]
+  //     M_{j+1} = [O += V(j) P(j); S(j+1) = K(j+1) Q^T]   (no S after the last tile)
+  // One barrier per tile.  Passing B_j, a wave knows that every wave has
+  // ended M_j -- so the buffers of K(j) and V(j-1), which K(j+2) and V(j+1)
+  // take, are free -- and that all of K(j+1) and V(j) has landed.  A load
+  // has a whole tile step until the barrier that waits for it.  The waves of
+  // a workgroup run the same phases together; what overlaps one's softmax
+  // with matrix-core work is the other workgroup of the CU, one wave of each
+  // on every SIMD.
+  // Items overlap: the next item is started right after B_{n-1}, ahead of the
+  // last tile's softmax and products, so that the round trips of an item's
+  // start run behind the end of the one before.  At B_{n-1} the K buffers and
+  // the V buffer of tile n-2 are free for the next item's K(0), K(1) and V(0)
+  // (the tile count runs on).  The finished O is stored after the next item's
+  // S, when nothing reads V(n-1) any more: that buffer is the transpose area
+  // of the stores until the next item's B_0 (each wave its own quarter, which
+  // only its own loads write).  The fused list is read only before B_{n-1},
+  // the item word between B_{n-1} and the next S.
+  auto ask = [&]() {  // (nothing is in flight)
+    __syncthreads();
+    if (tid == 0) {
+      s_item = qsel < 8u ? resolve(take()) : kNoItem;
+      wait_lgkmcnt0();
+    }
+    __syncthreads();
+    w = __builtin_amdgcn_readfirstlane(s_item);
+    __syncthreads();
+  };
+  for (;;) {
+  bool started = false;
+  for (;;) {
+    if (w == kAsk) ask();
+    if (w == kNoItem) break;
+    started = start_item();
+    if (started) break;
+    w = next_static();  // (an item without work)
+  }
+  if (!started) break;
+  bool have_prev = false;  // a finished item's O is still to be stored
+  int p_row0 = 0, p_rem0 = 0, p_kvh = 0, p_valid = 0;
+  for (;;) {
+    wait_vmcnt<0>();
+    bare_barrier();  // S
+    if constexpr (kIsFused) n_tiles = T_s + __builtin_amdgcn_readfirstlane(f_count);
+    // The next item: a number is asked for here and read after B_{n-1}.
+    w = next_static();
+    unsigned ticket = 0;
+    if (tid == 0 && w == kAsk && qsel < 8u) ticket = take();
+    if (have_prev) store_item(p_row0, p_rem0, p_kvh, p_valid, v_at(1) + wave * kSlabBytes);
+    if (w == kAsk && tid == 0) {
+      s_item = resolve(ticket);
+      wait_lgkmcnt0();
+    }
 #pragma unroll
     for (int dt = 0; dt < kDt; ++dt)
 #pragma unroll
       for (int i = 0; i < 16; ++i) o[dt][i] = 0.f;
-    float m_used = -INFINITY;  // max (log2 units) the exponentials of this column are taken against
-    float l_run = 0.f;         // this lane half's share of the column's exponential sum
-    const size_t prow = qrow / D;  // (query row, q head) of this lane's column
+#pragma unroll
+    for (int dt = 0; dt < kDt; ++dt) asm volatile("" : "+v"(o[dt]));  // (no shared tuple of zeros)
+    m_used = -INFINITY;
+    l_run = 0.f;
     if constexpr (MODE == kSuffix) {
-      // Continue from the shared half's state (loaded with Q, waited for with
-      // the first tiles).  Lane half 0 carries the whole sum.
+      // Continue from the shared half's state.  Lane half 0 carries the whole sum.
+      const size_t prow = row_of(row0, rem0, kvh, min(wave * kColsPerWave + n, n_valid - 1)) / D;
       m_used = part_ml[prow * 2];
       l_run = hh == 0 ? part_ml[prow * 2 + 1] : 0.f;
 #pragma unroll
@@ -484,434 +921,114 @@ __global__ __launch_bounds__(kThreads, 1) void paged_attn_kernel(
           for (int e = 0; e < 4; ++e) o[dt][g4 * 4 + e] = v[e];
         }
     }
-    bf16x8 pb[kTileBlocks];    // P of the tile whose V^T P^T is still due
-    f32x16 sc0, sc1;           // scores of the tile whose softmax is next
-
-    // Softmax step of the score tile starting at key j0: causal mask, then
-    // P = exp2(S * scale_log2 - m_used), rounded to bf16 for the V^T P^T
-    // product while the row sum adds the fp32 values.  m_used is the column
-    // max the exponentials were last rescaled to.  The step is accepted as
-    // long as every lane's sum of its exponentials lies in [0, 2^8] (so no
-    // single one exceeds 2^8, the headroom the fp32 accumulators are given);
-    // otherwise -- on the first tile (`first`: m_used is still -inf), or when
-    // the max has grown -- the tile's column max is taken, O and the sum are
-    // rescaled to it and the exponentials recomputed.
-    // Lane half hh holds keys j0 + (e>>3)*16 + 8*hh + (e&7) [+32] of the tile.
-    auto softmax = [&](int j0, bool first, int fused_thr) __attribute__((always_inline)) {
-      if (MODE == kFused && fused_thr != INT_MAX) {  // a request tile: its own rows, causal
-        const int rel = fused_thr;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int k = (e >> 3) * 16 + (e & 7);
-          sc0[e] = k > rel ? -INFINITY : sc0[e];
-          sc1[e] = k + 32 > rel ? -INFINITY : sc1[e];
-        }
-      }
-      if (MODE != kShared && MODE != kFused && j0 + kKeys - 1 > wave_pos_min) {  // causal
-        const int rel = pos - j0 - hh * 8;  // key (e>>3)*16 + (e&7) [+32] is visible iff <= rel
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int k = (e >> 3) * 16 + (e & 7);
-          sc0[e] = k > rel ? -INFINITY : sc0[e];
-          sc1[e] = k + 32 > rel ? -INFINITY : sc1[e];
-        }
-      }
-      if (MODE == kShared && j0 + kKeys > key_lim) {  // keys past the shared prefix
-        int lim = key_lim - j0 - hh * 8;
-        asm volatile("" : "+v"(lim));  // computed here: hoisted, the 32 compares would pin 64 SGPRs
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int k = (e >> 3) * 16 + (e & 7);
-          sc0[e] = k >= lim ? -INFINITY : sc0[e];
-          sc1[e] = k + 32 >= lim ? -INFINITY : sc1[e];
-        }
-      }
-      if (MODE == kSuffix && j0 < kv_split) {  // keys of the shared prefix: done before
-        int lo = kv_split - j0 - hh * 8;
-        asm volatile("" : "+v"(lo));  // as above
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int k = (e >> 3) * 16 + (e & 7);
-          sc0[e] = k < lo ? -INFINITY : sc0[e];
-          sc1[e] = k + 32 < lo ? -INFINITY : sc1[e];
-        }
-      }
-      // Exponentials against the running max m_used, summed per lane half.
-      auto exps = [&](float* ls) {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(sc0[e], scale_log2, -m_used));
-          const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(sc1[e], scale_log2, -m_used));
-          pb[e >> 3][e & 7] = (__bf16)p0;
-          pb[2 + (e >> 3)][e & 7] = (__bf16)p1;
-          ls[e & 3] = e < 4 ? p0 + p1 : ls[e & 3] + (p0 + p1);
-        }
-        // The bf16 operands are formed here, not after the acceptance test:
-        // sunk past it, all 32 fp32 exponentials would stay live across it.
-        asm volatile("" : "+v"(pb[0]), "+v"(pb[1]), "+v"(pb[2]), "+v"(pb[3]));
-      };
-      float ls[4];
-      float tsum = 0.f;
-      bool slow = first;
-      if (!first) {
-        exps(ls);
-        tsum = (ls[0] + ls[1]) + (ls[2] + ls[3]);
-        // Accepted unless some lane's sum exceeds kSumLimit or is not a
-        // number (an overflow, or -inf - -inf).
-        slow = __ballot(!(tsum <= kSumLimit)) != 0;
-      }
-      if (slow) {
-        float mx, mx2;
-        asm("v_max3_f32 %0, %1, %2, %3\n\t"
-            "v_max3_f32 %0, %0, %4, %5\n\t"
-            "v_max3_f32 %0, %0, %6, %7\n\t"
-            "v_max3_f32 %0, %0, %8, %9\n\t"
-            "v_max3_f32 %0, %0, %10, %11\n\t"
-            "v_max3_f32 %0, %0, %12, %13\n\t"
-            "v_max3_f32 %0, %0, %14, %15\n\t"
-            "v_max3_f32 %0, %0, %16, %17"
-            : "=&v"(mx)
-            : "v"(sc0[0]), "v"(sc1[0]), "v"(sc0[1]), "v"(sc1[1]), "v"(sc0[2]), "v"(sc1[2]), "v"(sc0[3]),
-              "v"(sc1[3]), "v"(sc0[4]), "v"(sc1[4]), "v"(sc0[5]), "v"(sc1[5]), "v"(sc0[6]), "v"(sc1[6]),
-              "v"(sc0[7]), "v"(sc1[7]), "v"(sc0[8]));
-        asm("v_max3_f32 %0, %1, %2, %3\n\t"
-            "v_max3_f32 %0, %0, %4, %5\n\t"
-            "v_max3_f32 %0, %0, %6, %7\n\t"
-            "v_max3_f32 %0, %0, %8, %9\n\t"
-            "v_max3_f32 %0, %0, %10, %11\n\t"
-            "v_max3_f32 %0, %0, %12, %13\n\t"
-            "v_max3_f32 %0, %0, %14, %15\n\t"
-            "v_max3_f32 %0, %0, %16, %0"
-            : "=&v"(mx2)
-            : "v"(mx), "v"(sc1[8]), "v"(sc0[9]), "v"(sc1[9]), "v"(sc0[10]), "v"(sc1[10]), "v"(sc0[11]),
-              "v"(sc1[11]), "v"(sc0[12]), "v"(sc1[12]), "v"(sc0[13]), "v"(sc1[13]), "v"(sc0[14]),
-              "v"(sc1[14]), "v"(sc0[15]), "v"(sc1[15]));
-        mx = mx2;
-        mx = max_across_halves(mx) * scale_log2;
-        const float m_new = fmaxf(m_used, mx);
-        const float alpha = __builtin_amdgcn_exp2f(m_used - m_new);
-        m_used = m_new;
-        l_run *= alpha;
-#pragma unroll
-        for (int dt = 0; dt < kDt; ++dt)
-#pragma unroll
-          for (int e = 0; e < 16; ++e) o[dt][e] *= alpha;
-        exps(ls);
-        tsum = (ls[0] + ls[1]) + (ls[2] + ls[3]);
-      }
-      l_run += tsum;
+    // kFused: the item's request numbers this wave's columns belong to.
+    const int ord_lo = kIsFused ? __builtin_amdgcn_readlane(my_ord, 0) : 0;
+    const int ord_hi = kIsFused ? __builtin_amdgcn_readlane(my_ord, 31) : 0;
+    // kFused: request number and tile of item tile tl (a request tile).
+    auto fused_entry = [&](int tl, int& o_, int& tt) {
+      const uint32_t e = __builtin_amdgcn_readfirstlane(f_tile[tl - T_s]);
+      o_ = int(e >> 24);
+      tt = int(e & 0xFFFFFFu);
     };
-
-    // One matrix-core phase: O += V(sV) P over the tile's pool blocks
-    // (kTileBlocks * kDt products), then S = K(sK) Q^T (2 * kDch products),
-    // as one software-pipelined stream whose LDS operands are read kPrefetch
-    // products ahead, so that a lone wave keeps the matrix core busy.
-    constexpr int kPvSteps = kTileBlocks * kDt, kQkSteps = 2 * kDch, kPrefetch = 4;
-    auto m_phase = [&](auto with_pv, auto with_qk, const uint8_t* sV, const uint8_t* sK) {
-      constexpr int first = decltype(with_pv)::value ? 0 : kPvSteps;
-      constexpr int last = decltype(with_qk)::value ? kPvSteps + kQkSteps : kPvSteps;
-      auto operand = [&](int st) -> bf16x8 {
-        if (st < kPvSteps) {
-          const int b = st / kDt, d = (st % kDt) * 32 + n;
-          return *(const bf16x8*)(sV + b * kVBlockBytes + d * 32 + (v_slot(d, hh) << 4));
+    // Whether some column of this wave meets tile tl of the item.
+    auto active = [&](int tl, int ord) {
+      if constexpr (kIsFused) return wave_active && (tl < T_s || (ord >= ord_lo && ord <= ord_hi));
+      return tl <= wave_last;
+    };
+    bool act = wave_active;
+    if (act) m_phase(no(), yes(), ring, k_at(0));
+    int cur_ord = 0, cur_tt = 0;  // kFused: request number and tile of item tile j (a shared one: itself)
+    int j0 = t0 * kKeys, thr = INT_MAX, next_ord = 0, next_tt = 0;
+    // First key and (kFused) mask threshold of tile j, and the zeroing of its V tail.
+    auto before_barrier = [&](int j) {
+      if constexpr (kIsFused) {
+        j0 = cur_tt * kKeys;
+        thr = INT_MAX;
+        next_ord = 0;
+        next_tt = j + 1;
+        if (j >= T_s) {
+          thr = cur_ord == my_ord ? my_pos - j0 - hh * 8 : -1;
+          const int lim = __builtin_amdgcn_readfirstlane(f_lim[cur_ord]);
+          if (j0 + kKeys > lim) zero_v_tail(j, j0, lim);
         }
-        const int u = st - kPvSteps, m = (u & 1) * 32 + n;
-        return *(const bf16x8*)(sK + m * kRowBytes + (k_slot<D>(m, (u >> 1) * 2 + hh) << 4));
-      };
-      // Raised issue priority for the phase: when the partner wave's softmax
-      // and this wave's next product are both ready, the product goes first,
-      // so the matrix core does not wait behind a run of vector instructions
-      // (1-2.5% faster than equal priority on llama8b, qwen7b, large and
-      // sweep100).  The scheduling barriers keep the phase's instructions
-      // between the two priority changes.
-      __builtin_amdgcn_sched_barrier(0);
-      __builtin_amdgcn_s_setprio(1);
-      __builtin_amdgcn_sched_barrier(0);
-      if constexpr (decltype(with_qk)::value) {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) { sc0[e] = 0.f; sc1[e] = 0.f; }
+        if (j + 1 >= T_s && j + 1 < n_tiles) fused_entry(j + 1, next_ord, next_tt);
+      } else {
+        j0 = (t0 + j) * kKeys;
+        if (j0 + kKeys > key_lim) zero_v_tail(j, j0, key_lim);
       }
-      bf16x8 buf[kPrefetch];
-#pragma unroll
-      for (int st = first; st < first + kPrefetch && st < last; ++st) buf[st % kPrefetch] = operand(st);
-#pragma unroll
-      for (int st = first; st < last; ++st) {
-        const bf16x8 a = buf[st % kPrefetch];
-        if (st + kPrefetch < last) buf[st % kPrefetch] = operand(st + kPrefetch);
-        if (st < kPvSteps) {
-          const int dt = st % kDt;
-          o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb[st / kDt], o[dt], 0, 0, 0);
+    };
+    for (int j = 0;; ++j) {
+      if (j > 0) wait_vmcnt<0>();  // (tile 0's were waited for before S; only stores follow them)
+      before_barrier(j);
+      bare_barrier();  // B_j
+      if (j == n_tiles - 1) break;
+      issue_v(j + 1, id_next);
+      if (j + 2 < n_tiles) {
+        id_next = usable(j + 2, raw_next);
+        issue_k(j + 2, id_next);
+      }
+      // The block id of tile j+3, two steps ahead of its use.  Its scalar load
+      // is waited for after the softmax (below), which reads no LDS, and not
+      // by the first LDS read of the matrix-core phase, which would then wait
+      // for all its operands in flight as well.
+      if (j + 3 < n_tiles) {
+        if constexpr (kIsFused) {
+          int o_ = 0, tt = j + 3, rr = 0;
+          if (j + 3 >= T_s) {
+            fused_entry(j + 3, o_, tt);
+            rr = __builtin_amdgcn_readfirstlane(f_req[o_]);
+          }
+          raw_next = scalar_load(block_tables + size_t(rr) * max_blocks + min(tt * kTileBlocks + wave, max_blocks - 1));
         } else {
-          const int u = st - kPvSteps;
-          if (u & 1) sc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[u >> 1], sc1, 0, 0, 0);
-          else sc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[u >> 1], sc0, 0, 0, 0);
+          raw_next = raw_id(j + 3);
         }
       }
-      // Pin the pipelined order for the scheduler (mask 0x100: LDS reads,
-      // 0x008: matrix-core ops): kPrefetch reads, then one product per read,
-      // then the last kPrefetch products.
-      constexpr int steps = last - first, lead = steps < kPrefetch ? steps : kPrefetch;
-      __builtin_amdgcn_sched_group_barrier(0x100, lead, 0);
-#pragma unroll
-      for (int st = 0; st < steps - lead; ++st) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      int jj = j;
+      asm volatile("" : "+s"(jj));  // keeps the first tile inside the loop (no second copy of its body)
+      if (act) {
+        mask(j0, thr);
+        softmax(MODE != kSuffix && jj == 0);
       }
-      __builtin_amdgcn_sched_group_barrier(0x008, lead, 0);
-      __builtin_amdgcn_sched_barrier(0);
-      __builtin_amdgcn_s_setprio(0);
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    using yes = std::true_type;
-    using no = std::false_type;
-
-    // Ping-pong schedule.  Every wave runs the same phase sequence
-    //   M_0 = [S(0) = K(0) Q^T]
-    //   V_0 = [softmax S(0) -> P(0)]
-    //   M_j = [O += V(j-1) P(j-1); S(j) = K(j) Q^T]   j = 1 .. n_tiles-1
-    //   V_j = [softmax S(j) -> P(j)]
-    //   M_n = [O += V(n-1) P(n-1)]
-    // with a workgroup barrier before every phase.  Waves kWaves/2 .. kWaves-1
-    // pass one extra barrier first (and waves 0 .. kWaves/2-1 one at the
-    // end), so the second half runs one phase behind the first: while one
-    // wave of a SIMD issues matrix-core work (M) its partner runs the vector
-    // softmax (V).
-    //
-    // Counting this item's barriers, the first half runs phase number p (M_j
-    // is p = 2j, V_j is p = 2j+1) after barrier p and the second half after
-    // barrier p+1.  Hence:
-    //   - every wave waits for its own loads of tile j before the barrier
-    //     that opens V_{j-1}: barrier 2j-1 or 2j, so all of tile j is in LDS
-    //     by barrier 2j, where the first half starts M_j;
-    //   - the V tail of tile j is zeroed at the start of M_j (after barrier
-    //     2j or 2j+1, once tile j is complete) and read in M_{j+1} (after
-    //     barrier 2j+2 or 2j+3);
-    //   - tile j+2 is issued at the start of V_j (after barrier 2j+1 or
-    //     2j+2), into the stage of tile j-2, whose last reader M_{j-1} ended
-    //     by barrier 2j everywhere.
-    // The ring thus holds tiles j-1 (V still due), j and j+1 (in flight
-    // since V_{j-1}) during M_j, and j+2 from V_j on.  The loads are issued
-    // in the softmax phase rather than at the start of M_j so that their
-    // issue stays off the matrix-core phase, which sets the pace: 2-7%
-    // faster on llama8b, qwen7b, large and the hit-rate sweep than issuing
-    // at M_j, with a tile of lead still enough that the waits stay short.
-    // Across items the stage count runs on: when the first half starts the
-    // next item, the second half may still be in M_n of this one, which
-    // reads the stage of tile n-1, while the next item's tiles 0, 1 and 2 go
-    // to the stages after it.
-    auto wait_tile = [&](int) { wait_vmcnt<0>(); };  // the newest loads of this wave are the tile's
-    auto begin_m = [&](int j) {
-      bare_barrier();
-      if (MODE == kFused && j == 0) {  // the item's list is complete (wave 0 waited before this barrier)
-        n_tiles = T_s + __builtin_amdgcn_readfirstlane(f_count);
-        wave_last = wave_active ? n_tiles - 1 : -1;
+      asm volatile("" : "+s"(raw_next));
+      // (S of a tile past the wave's last one is computed and ignored.)
+      if (act) m_phase(yes(), yes(), v_at(j), k_at(j + 1));
+      const bool act_next = active(j + 1, next_ord);
+      if constexpr (kIsFused) {
+        if (!act && act_next) m_phase(no(), yes(), ring, k_at(j + 1));
       }
-      if (MODE == kFused && j >= T_s && j < n_tiles) {
-        const int i = j - T_s;
-        const int tt = __builtin_amdgcn_readfirstlane(f_tt[i]), lim = __builtin_amdgcn_readfirstlane(f_lim[i]);
-        if (tt * kKeys + kKeys > lim) {
-          zero_v_tail(tt * kKeys, stage(j) + kKTileBytes, lim);
-          wait_lgkmcnt0();
-        }
-      } else if (MODE != kFused && j < n_tiles && (t0 + j) * kKeys + kKeys > key_lim) {
-        zero_v_tail((t0 + j) * kKeys, stage(j) + kKTileBytes, key_lim);
-        wait_lgkmcnt0();  // zeros in LDS before the next barrier
-      }
-    };
-    // The block id of tile j+3 (issued in V_{j+1}) is loaded at the start of
-    // V_j, right after tile j+2 is issued with the previous one: no LDS read
-    // follows until the next phase, so the scalar load (which shares lgkmcnt
-    // with LDS reads) has landed before anything waits on lgkmcnt.
-    auto prefetch_id = [&](int j) {
-      if (j + 3 < n_tiles) raw_next = MODE == kFused ? fused_raw(j + 3) : raw_id(j + 3);
-    };
-
-    issue_tile(0, raw_id0);
-    if (1 < n_tiles) issue_tile(1, raw_id1);
-    // kFused: with the first tiles and Q in flight, find the requests of the
-    // item's rows, this lane's request and position, and (wave 0) the list of
-    // request tiles; tiles 0-2 are shared, so request 0's table gave their ids.
-    // Scalar loads only: they do not queue behind the tiles' vector loads.
-    if constexpr (MODE == kFused) {
-      const int row_a = col0 / G, row_b = min(col0 + kCols - 1, n_cols - 1) / G;
-      // r_a: the largest request whose first row is at or before row_a
-      int lo = 0, hi = n_req;  // cu_q[lo] <= row_a < cu_q[hi]
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (cu_q[mid] <= row_a) lo = mid;
-        else hi = mid;
-      }
-      r_a = lo;
-      const int col_l = min(col0 + wave * kColsPerWave + n, n_cols - 1);
-      const int row_l = col_l / G;
-      int n_list = 0;
-      // requests r_a, r_a + 1, ... while their rows start at or before row_b
-      for (int rr = r_a; rr < n_req; ++rr) {
-        const int b0 = cu_q[rr];
-        if (b0 > row_b) break;
-        const int b1 = cu_q[rr + 1];
-        const int lo_row = max(b0, row_a), hi_row = min(b1 - 1, row_b);
-        if (lo_row > hi_row) continue;  // no row of this item (or an empty request)
-        const int Lr = min(seq_lens[rr], max_blocks * kBlock);
-        if (row_l >= b0 && row_l < b1) {
-          my_rel = rr - r_a;
-          my_pos = Lr - (b1 - b0) + (row_l - b0);
-        }
-        // keys the item's rows of rr see end at lim; its tiles T_s .. go to the list
-        const int lim = Lr - (b1 - b0) + (hi_row - b0) + 1;
-        const int cnt = min(max(0, (lim + kKeys - 1) / kKeys - T_s), kFusedTiles - n_list);
-        if (wave == 0) {
-          for (int k = lane; k < cnt; k += 64) {
-            f_rel[n_list + k] = rr - r_a;
-            f_tt[n_list + k] = T_s + k;
-            f_lim[n_list + k] = lim;
-          }
-        }
-        n_list += cnt;
-      }
-      if (wave == 0) {
-        if (lane == 0) f_count = n_list;
-        wait_lgkmcnt0();  // the list is in LDS before the barrier that opens M_0
-      }
+      act = act_next;
+      cur_ord = next_ord;
+      cur_tt = next_tt;
     }
-    if (tid == 0) {  // the next item, fetched while the first tiles load
-      s_item[(it + 1) & 1] = fetch();
-      wait_lgkmcnt0();
-    }
-    // Q and tiles 0 and 1 in (before the second half's extra barrier, which
-    // stands in for the barrier opening V_{-1}).
-    wait_vmcnt<0>();
-    if (lag) bare_barrier();
-    // kFused: mask threshold of item tile j for this lane (INT_MAX: a shared
-    // tile, all keys visible) and the tile's first key in its request.
-    auto fused_thr = [&](int j, int& j0) {
-      if (j < T_s) {
-        j0 = j * kKeys;
-        return INT_MAX;
-      }
-      const int rel = __builtin_amdgcn_readfirstlane(f_rel[j - T_s]);
-      j0 = __builtin_amdgcn_readfirstlane(f_tt[j - T_s]) * kKeys;
-      return rel == my_rel ? my_pos - j0 - hh * 8 : -1;
-    };
-    auto soft = [&](int j, bool first) __attribute__((always_inline)) {
-      if constexpr (MODE == kFused) {
-        int j0;
-        const int th = fused_thr(j, j0);
-        softmax(j0, first, th);
-      } else {
-        softmax((t0 + j) * kKeys, first, INT_MAX);
-      }
-    };
-    begin_m(0);
-    if (0 <= wave_last) m_phase(no(), yes(), stage(0), stage(0));
-    if (n_tiles > 1) wait_tile(1);
-    bare_barrier();
-    if (2 < n_tiles) issue_tile(2, raw_next);
-    prefetch_id(0);
-    if (0 <= wave_last) soft(0, MODE != kSuffix);
-    for (int j = 1; j < n_tiles; ++j) {
-      begin_m(j);
-      // Tiles past the wave's last visible key are skipped; the step right
-      // after it still adds P(j-1) (its S(j) product is wasted and ignored).
-      if (j - 1 <= wave_last) m_phase(yes(), yes(), stage(j - 1) + kKTileBytes, stage(j));
-      if (j + 1 < n_tiles) wait_tile(j + 1);
-      bare_barrier();
-      if (j + 2 < n_tiles) issue_tile(j + 2, raw_next);
-      prefetch_id(j);
-      if (j <= wave_last) soft(j, false);
-    }
-    begin_m(n_tiles);
-    if (n_tiles - 1 <= wave_last) m_phase(yes(), no(), stage(n_tiles - 1) + kKTileBytes, stage(0));
-    if (!lag) bare_barrier();
+    if (act) mask(j0, thr);
+    const bool first = MODE != kSuffix && n_tiles == 1;
+    const uint8_t* v_last = v_at(n_tiles - 1);
     tbase += n_tiles;
-
-    if (wave_active) {
-      const float l_tot = l_run + __shfl_xor(l_run, 32);
-      if constexpr (MODE == kShared) {  // unnormalised O, max and sum for the suffix half
-        if (col_valid) {
-          if (hh == 0) {
-            part_ml[prow * 2] = m_used;
-            part_ml[prow * 2 + 1] = l_tot;
-          }
-#pragma unroll
-          for (int dt = 0; dt < kDt; ++dt)
-#pragma unroll
-            for (int g4 = 0; g4 < 4; ++g4) {
-              const f32x4 v = {o[dt][g4 * 4], o[dt][g4 * 4 + 1], o[dt][g4 * 4 + 2], o[dt][g4 * 4 + 3]};
-              *(f32x4*)(part_o + prow * D + dt * 32 + g4 * 8 + hh * 4) = v;
-            }
-        }
-      } else if constexpr (D == 128) {
-        // The normalised O leaves through LDS.  In the matrix-core layout a
-        // lane holds 8-byte pieces of one output row, so direct stores put 16
-        // bytes of 32 different rows into every instruction; those scattered
-        // stores held up the item boundary (timed without them, llama8b and
-        // large ran 16% and 8% faster).  Each wave writes its 32 rows, 64
-        // dimensions at a time, into its 4 KiB of the ring stage the next
-        // item's tile 2 will take, then stores whole 128-byte half rows, 8
-        // lanes per half row.  That stage (tile n-2's) is free: its last
-        // reader M_{n-1} ended by barrier 2n everywhere, and the next item
-        // writes it only in its V_0, after both halves have passed here.
-        // 16-byte chunks are XOR-swizzled by row against bank conflicts.
-        const float inv = 1.f / l_tot;
-        uint8_t* tb = stage(2) + wave * (kStageBytes / kWaves);
-        static_assert(kStageBytes / kWaves >= kColsPerWave * 128, "transpose area");
-        size_t orow4[4];  // output row of the 4 rows this lane stores
-        bool ok4[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int c = col0 + wave * kColsPerWave + r * 8 + (lane >> 3);
-          ok4[r] = c < n_cols;
-          const int tr = c / G;
-          orow4[r] = (size_t(q0 + tr) * Hq + size_t(kvh) * G + (c - tr * G)) * D;
-        }
-        const int ch_r = lane & 7;
-#pragma unroll
-        for (int p = 0; p < kDt / 2; ++p) {
-#pragma unroll
-          for (int dl = 0; dl < 2; ++dl)
-#pragma unroll
-            for (int g4 = 0; g4 < 4; ++g4) {
-              bf16x4 v;
-#pragma unroll
-              for (int e = 0; e < 4; ++e) v[e] = (__bf16)(o[2 * p + dl][g4 * 4 + e] * inv);
-              const int ch = dl * 4 + g4;
-              *(bf16x4*)(tb + n * 128 + ((ch ^ (n & 7)) << 4) + hh * 8) = v;
-            }
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int row = r * 8 + (lane >> 3);
-            const u32x4 val = *(const u32x4*)(tb + row * 128 + ((ch_r ^ (row & 7)) << 4));
-            if (ok4[r]) *(u32x4*)(out + orow4[r] + p * 64 + ch_r * 8) = val;
-          }
-        }
-      } else {
-        const float inv = 1.f / l_tot;
-        if (col_valid) {
-          uint16_t* orow = out + qrow;
-#pragma unroll
-          for (int dt = 0; dt < kDt; ++dt)
-#pragma unroll
-            for (int g4 = 0; g4 < 4; ++g4) {
-              bf16x4 v;
-#pragma unroll
-              for (int e = 0; e < 4; ++e) v[e] = (__bf16)(o[dt][g4 * 4 + e] * inv);
-              *(bf16x4*)(orow + dt * 32 + g4 * 8 + hh * 4) = v;
-            }
-        }
-      }
+    p_row0 = row0;
+    p_rem0 = rem0;
+    p_kvh = kvh;
+    p_valid = n_valid;
+    if (w == kAsk) w = __builtin_amdgcn_readfirstlane(s_item);
+    started = w != kNoItem && start_item();
+    if (!started && w != kNoItem) w = next_static();  // (an item without work)
+    if (act) {
+      softmax(first);
+      m_phase(yes(), no(), v_last, ring);
     }
+    if (!started) break;
+    have_prev = true;
+  }
+  store_item(p_row0, p_rem0, p_kvh, p_valid, ring + wave * kSlabBytes);
   }
 
-  // Every queue is drained.  The last workgroup out clears the counters for
-  // the next call on this workspace (no workgroup fetches any more by then).
-  // The exit count needs no fence.  Wave 0 (which made every queue atomic of
-  // this workgroup) first waits until all its memory operations have
+  // (stealing) Every queue is drained.  The last workgroup out clears the
+  // counters for the next call on this workspace (no workgroup asks any more by
+  // then).  The exit count needs no fence.  Wave 0 (which made every queue
+  // atomic of this workgroup) first waits until all its memory operations have
   // completed, so once the last workgroup sees the full count no queue atomic
-  // of this launch is in flight.  An acquire-release count, with its L2
-  // write-back and invalidate at every workgroup's exit, cost 2-5% of the
-  // short launches.  The outputs are published by the end of the kernel.
-  if (tid == 0 && qsel != 9u) {  // (qsel is 9 only in the one-item-each mode)
+  // of this launch is in flight.  The outputs are published by the end of the
+  // kernel.
+  if (stealing && tid == 0) {
     wait_vmcnt<0>();
     const unsigned done =
         __hip_atomic_fetch_add(queue + kDoneWord, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1060,17 +1177,27 @@ int launch_attn(const char* fn, const uint16_t* q, const uint16_t* k_pool, const
                 float* part_ml, int part_rows, hipStream_t s) {
   const int64_t items = col_tiles * Hkv * (MODE == kShared || MODE == kFused ? 1 : B);
   if (items == 0) return ILPC_OK;
+  if (items >= int64_t(kAsk)) return ilpc::set_error(ILPC_EUNSUP, "%s: grid too large", fn);
   const int cus = device_cus();
   if (cus <= 0) return ilpc::set_error(ILPC_EHIP, "%s: cannot query the device", fn);
-  const unsigned grid = unsigned(items < cus ? items : cus);
+  const int64_t wgs = int64_t(wgs_per_cu(D)) * cus;
+  const unsigned grid = unsigned(items < wgs ? items : wgs);
+  // Chunks of the item numbers dealt to the XCDs' queues in turn: whole
+  // (request, kv head) pairs, whose items read the same K/V, when they deal out
+  // evenly (or nearly so), else pieces that do.
+  const int64_t pairs = items / col_tiles;
+  const unsigned chunk = unsigned(
+      items >= int64_t(kLongRounds) * grid ? (items + 7) / 8
+      : pairs % 8 == 0 || pairs >= 256     ? col_tiles
+                                           : std::max<int64_t>(items / 256, 1));
   if (D == 128)
     hipLaunchKernelGGL((paged_attn_kernel<128, MODE>), dim3(grid), dim3(kThreads), 0, s, q, k_pool, v_pool,
                        num_blocks, block_tables, max_blocks, cu_q, seq_lens, B, Hq, Hkv, int(col_tiles),
-                       unsigned(items), scale_log2, out, queue, kv_split, part_o, part_ml, part_rows);
+                       unsigned(items), chunk, scale_log2, out, queue, kv_split, part_o, part_ml, part_rows);
   else
     hipLaunchKernelGGL((paged_attn_kernel<64, MODE>), dim3(grid), dim3(kThreads), 0, s, q, k_pool, v_pool,
                        num_blocks, block_tables, max_blocks, cu_q, seq_lens, B, Hq, Hkv, int(col_tiles),
-                       unsigned(items), scale_log2, out, queue, kv_split, part_o, part_ml, part_rows);
+                       unsigned(items), chunk, scale_log2, out, queue, kv_split, part_o, part_ml, part_rows);
   return launch_status(fn);
 }
 
