@@ -243,16 +243,22 @@ int ilpc_rope_kv_append(const uint16_t* q, uint16_t* q_out, int32_t Hq, const ui
  * to the cached KV of its whole context): the same operation, arguments,
  * layouts and bounds rules as ilpc_paged_prefill_attn, for batches whose
  * max_q_len * (Hq / Hkv) <= 32 (ILPC_EUNSUP otherwise).  One wave per
- * (request, kv head) pair streams that request's K/V blocks from the pools;
+ * (request, kv head) pair -- up to eight where the pairs are too few to fill
+ * the chip -- streams that request's K/V blocks from the pools;
  * results agree with ilpc_paged_prefill_attn to the attention tolerance, not
  * bit for bit.  ilpc_paged_prefill_attn takes this path by itself for such
- * batches: split as ilpc_decode_split() says when its workspace has room for
- * the partials, else unsplit when B * Hkv >= the device's compute units.
+ * batches: split as for n_split = 0 when its workspace has room for
+ * ilpc_decode_split() ranges, else unsplit when B * Hkv >= the device's
+ * compute units; and for longer queries with few columns in the whole batch
+ * (B * Hkv * ceil(max_q_len * Hq / Hkv / 32) <= 512) over contexts that may
+ * reach 1024 keys (16 * max_blocks).
  *
  * n_split      [host] key ranges per pair, 1 .. 64, or 0 for
- *                     ilpc_decode_split()'s choice.  With n > 1 each range is
- *                     one wave; the ranges' partial results (fp32) go to the
- *                     workspace and a second kernel merges them, so that
+ *                     the library's choice (at most ilpc_decode_split()).
+ *                     With n > 1 the pair's keys are cut into at least n
+ *                     ranges, up to eight to a workgroup, which merges them;
+ *                     past 8 the workgroups' partial results (fp32) go to the
+ *                     workspace and a second kernel merges those, so that
  *                     batches with few pairs still occupy the whole chip.
  * workspace    [device] >= ilpc_decode_workspace_bytes(..., n) bytes,
  *                     16-byte aligned, no initial contents needed (NULL with
@@ -267,11 +273,12 @@ int ilpc_paged_decode_attn(const uint16_t* q, const uint16_t* k_pool, const uint
                            uint16_t* out, int32_t n_split, void* workspace, size_t workspace_bytes,
                            void* stream);
 
-/* The key-range count ilpc_paged_decode_attn uses for n_split = 0 on the
- * current device: 1 when B * Hkv >= its SIMDs (4 per compute unit), and
- * when B * Hkv >= half of them with a context bound 16 * max_blocks under
- * 1024 tokens; otherwise enough ranges for one wave per SIMD, at most one
- * per 32 keys of that bound, at most 64. */
+/* The most key ranges with partial results in the workspace that
+ * ilpc_paged_decode_attn takes for n_split = 0 on the current device: 1 when
+ * B * Hkv >= its SIMDs (4 per compute unit), and when B * Hkv >= half of them
+ * with a context bound 16 * max_blocks under 1024 tokens; otherwise enough
+ * ranges for one wave per SIMD, at most one per 32 keys of that bound, at most
+ * 64. */
 int ilpc_decode_split(int32_t B, int32_t Hkv, int32_t max_blocks, int32_t* n_split);
 
 /* Workspace bytes of ilpc_paged_decode_attn with n_split ranges:

@@ -5,7 +5,8 @@
 // the cached KV of its whole context.  With one to a few query rows per
 // request the work is bound by reading K and V from HBM, not by the matrix
 // cores, so this kernel drops the workgroup-shared LDS ring of the prefill
-// kernel: every wave owns one (request, kv head) and streams that request's K
+// kernel: every wave owns one (request, kv head) -- or, where the batch has too
+// few of these to fill the chip, a range of its keys -- and streams that K
 // and V blocks straight from the pools into registers, two 16-token pool
 // blocks (32 keys) per step, with the next step's loads in flight while the
 // current one is computed.  The G query heads of the kv head times the
@@ -39,7 +40,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBlock = 16;
 constexpr int kStepKeys = 32;        // keys per step (two pool blocks)
-constexpr int kWavesPerGroup = 4;
+constexpr int64_t kFill = 2048;       // waves the chip holds (256 CUs x 4 SIMDs x 2)
 constexpr float kLazyRescale = 8.f;  // log2 growth of a column max tolerated before rescaling O
 
 // Key held by MFMA row m of a step: inside every 16 keys the groups [4,8)
@@ -63,17 +64,29 @@ struct StepRegs {
   u32x4 v[2][D / 32];   // V^T operand, [pool block of the step][32-dimension tile]
 };
 
-template <int D>
-__global__ __launch_bounds__(64 * kWavesPerGroup, 2) void decode_attn_kernel(
+// Waves of a workgroup whose waves work W to a (request, kv head) pair.
+constexpr int group_waves(int W) { return W > 4 ? W : 4; }
+
+// W waves of the workgroup (1, 2, 4 or 8) share a (request, kv head) pair's 32
+// query columns: each takes its share of the steps, and their partial results
+// are merged through LDS at the end.
+template <int D, int W>
+__global__ __launch_bounds__(64 * group_waves(W), 2) void decode_attn_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_pool,
     const uint16_t* __restrict__ v_pool, int num_blocks, const int32_t* __restrict__ block_tables,
     int max_blocks, const int32_t* __restrict__ cu_q, const int32_t* __restrict__ seq_lens, int n_req,
-    int max_q_len, int Hq, int Hkv, float scale_log2, uint16_t* __restrict__ out, int n_split,
+    int max_q_len, int Hq, int Hkv, float scale_log2, uint16_t* __restrict__ out, int n_ct, int n_split,
     int cols_cap, float* __restrict__ part_o, float* __restrict__ part_ml) {
-  constexpr int kDch = D / 16, kDt = D / 32;
+  constexpr int kDch = D / 16, kDt = D / 32, kWavesPerGroup = group_waves(W);
   // Each wave's Q^T operand lives in LDS (read once per product), which keeps
   // two steps of K/V loads plus O within the registers of two waves per SIMD.
-  __shared__ u32x4 q_lds[kWavesPerGroup][kDch][64];
+  // For the merge (W > 1) the same space then holds every wave's O, one row of
+  // kRow floats per query column (4 more than D: rows start in other banks).
+  constexpr int kRow = D + 4, kCols = 32;
+  constexpr int kQBytes = kWavesPerGroup * kDch * 64 * 16, kOBytes = kWavesPerGroup * kCols * kRow * 4;
+  __shared__ __attribute__((aligned(16))) uint8_t lds[W > 1 && kOBytes > kQBytes ? kOBytes : kQBytes];
+  __shared__ float s_m[kWavesPerGroup][kCols], s_l[kWavesPerGroup][kCols];
+  u32x4(*q_lds)[kDch][64] = reinterpret_cast<u32x4(*)[kDch][64]>(lds);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 31, hh = lane >> 5;
@@ -86,35 +99,54 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void decode_attn_kernel(
   const unsigned nb = gridDim.x, per = nb >> 3, extra = nb & 7u;
   const unsigned x = blockIdx.x & 7u, i = blockIdx.x >> 3;
   const unsigned group = x * per + min(x, extra) + i;
-  const int item = int(group) * kWavesPerGroup + wave;
-  if (item >= n_req * Hkv * n_split) return;
-  // With n_split > 1 the pair's steps are cut into n_split consecutive ranges,
-  // one per wave; each wave leaves its unnormalised O, max and sum in
-  // part_o / part_ml for decode_combine_kernel (cols_cap = max_q_len * G columns per split).
-  const int sp = item % n_split, pair = item / n_split;
+  const int item = int(group) * (kWavesPerGroup / W) + wave / W;
+  const int n_items = n_req * Hkv * n_split * n_ct;
+  if (W == 1 && item >= n_items) return;
+  // The pair's steps are cut into n_split * W consecutive ranges, one per
+  // wave.  With n_split > 1 each workgroup leaves its pair's unnormalised O,
+  // max and sum in part_o / part_ml for decode_combine_kernel (cols_cap =
+  // max_q_len * G columns per split).
+  // Batches with more than 32 columns a pair (n_ct > 1 column tiles of 32) are
+  // not split further.
+  const bool in_grid = item < n_items;
+  const int ct = in_grid ? item % n_ct : 0, rest = in_grid ? item / n_ct : 0;
+  const int sp = rest % n_split, pair = rest / n_split;
   const int r = pair / Hkv, h = pair % Hkv;
   const int G = Hq / Hkv;
 
   const int q0 = cu_q[r], q_len = cu_q[r + 1] - q0;
   const int L = min(seq_lens[r], max_blocks * kBlock);
-  // rows past max_q_len are not computed (the host bounds max_q_len * G by 32)
-  const int n_cols = min(q_len, max_q_len) * G;
-  if (q_len <= 0 || q_len > L || n_cols > 32) return;
+  // rows past max_q_len are not computed
+  const int col0 = ct * kCols, n_cols = min(min(q_len, max_q_len) * G - col0, kCols);
+  const bool valid = in_grid && q_len > 0 && q_len <= L && n_cols > 0;
+  if (W == 1 && !valid) return;
 
+  f32x16 o[kDt];
+#pragma unroll
+  for (int dt = 0; dt < kDt; ++dt)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) o[dt][e] = 0.f;
+  float m_run = -INFINITY, l_run = 0.f;
+  bool col_valid = false;
+  size_t qrow = 0;
+  if (valid) {
   // This lane's query column (padding columns repeat the last valid one).
-  const bool col_valid = n < n_cols;
-  const int colc = col_valid ? n : n_cols - 1;
+  col_valid = n < n_cols;
+  const int colc = col0 + (col_valid ? n : n_cols - 1);
   const int t = colc / G;
   const int pos = L - q_len + t;  // keys 0 .. pos are visible to this column
-  const size_t qrow = (size_t(q0 + t) * Hq + size_t(h) * G + (colc - t * G)) * D;
+  qrow = (size_t(q0 + t) * Hq + size_t(h) * G + (colc - t * G)) * D;
 #pragma unroll
   for (int kc = 0; kc < kDch; ++kc) q_lds[wave][kc][lane] = *(const u32x4*)(q + qrow + kc * 16 + hh * 8);
 
   const int32_t* bt = block_tables + size_t(r) * max_blocks;
   const int n_blk = (L + kBlock - 1) / kBlock;
-  const int n_steps_all = (L + kStepKeys - 1) / kStepKeys;
-  const int steps_per = (n_steps_all + n_split - 1) / n_split;
-  const int s_begin = min(sp * steps_per, n_steps_all);
+  // keys past the last column's position are not visited (and their V rows zeroed)
+  const int key_end = L - q_len + (col0 + n_cols - 1) / G + 1;
+  const int n_steps_all = (key_end + kStepKeys - 1) / kStepKeys;
+  const int n_ranges = n_split * W, range = sp * W + wave % W;
+  const int steps_per = (n_steps_all + n_ranges - 1) / n_ranges;
+  const int s_begin = min(range * steps_per, n_steps_all);
   const int n_steps = min(s_begin + steps_per, n_steps_all);  // this wave runs steps s_begin .. n_steps-1
   const int krow = key_of_row(n);  // key of the step this lane's K operand row holds
   const size_t head_off = size_t(h) * kBlock * D;
@@ -163,13 +195,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void decode_attn_kernel(
     }
   };
 
-  f32x16 o[kDt];
-#pragma unroll
-  for (int dt = 0; dt < kDt; ++dt)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) o[dt][e] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
-  const int mask_from = L - q_len;  // steps reaching past this key need the causal mask
+  const int mask_from = L - q_len + col0 / G;  // steps reaching past this key need the causal mask
 
   auto compute = [&](int s, StepRegs<D>& R) {
     const int j0 = s * kStepKeys;
@@ -182,12 +208,12 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void decode_attn_kernel(
                                                   0, 0, 0);
     if (j0 + kStepKeys - 1 > mask_from) {
       // causal mask (keys past pos, which also covers keys >= L), and the V
-      // rows of keys >= L zeroed: unwritten pool slots may hold any bits
+      // rows of keys >= key_end zeroed: unwritten pool slots may hold any bits
       const int rel = pos - j0 - hh * 8;
 #pragma unroll
       for (int e = 0; e < 16; ++e)
         if ((e >> 3) * 16 + (e & 7) > rel) sc[e] = -INFINITY;
-      const int lim = L - j0 - hh * 8;  // keys b * 16 + e of this lane's V operand are valid iff < lim
+      const int lim = key_end - j0 - hh * 8;  // keys b * 16 + e of this lane's V operand are valid iff < lim
 #pragma unroll
       for (int b = 0; b < 2; ++b)
 #pragma unroll
@@ -253,40 +279,98 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void decode_attn_kernel(
     __builtin_amdgcn_sched_barrier(0);
   }
   if (s < n_steps) compute(s, ra);
+  }
 
   const float l_tot = l_run + __shfl_xor(l_run, 32);
-  if (n_split > 1) {
-    // partial state of this (pair, split), valid columns only: O [cols_cap][D]
-    // (unnormalised) in part_o, (max, sum) [cols_cap][2] in part_ml
+  if constexpr (W == 1) {
+    if (n_split > 1) {
+      // partial state of this (pair, split), valid columns only: O [cols_cap][D]
+      // (unnormalised) in part_o, (max, sum) [cols_cap][2] in part_ml
+      if (col_valid) {
+        const size_t slot = (size_t(pair) * n_split + sp) * size_t(cols_cap) + n;
+        float* po = part_o + slot * D;
+#pragma unroll
+        for (int dt = 0; dt < kDt; ++dt)
+#pragma unroll
+          for (int g4 = 0; g4 < 4; ++g4) {
+            const f32x4 v = {o[dt][g4 * 4], o[dt][g4 * 4 + 1], o[dt][g4 * 4 + 2], o[dt][g4 * 4 + 3]};
+            *(f32x4*)(po + dt * 32 + g4 * 8 + hh * 4) = v;
+          }
+        if (hh == 0) {
+          part_ml[slot * 2] = m_run;
+          part_ml[slot * 2 + 1] = l_tot;
+        }
+      }
+      return;
+    }
     if (col_valid) {
-      const size_t slot = (size_t(pair) * n_split + sp) * size_t(cols_cap) + n;
-      float* po = part_o + (slot - n) * D;  // row n of this (pair, split)
+      const float inv = 1.f / l_tot;
+      uint16_t* orow = out + qrow;
+#pragma unroll
+      for (int dt = 0; dt < kDt; ++dt)
+#pragma unroll
+        for (int g4 = 0; g4 < 4; ++g4) {
+          bf16x4 v;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = (__bf16)(o[dt][g4 * 4 + e] * inv);
+          *(bf16x4*)(orow + dt * 32 + g4 * 8 + hh * 4) = v;
+        }
+    }
+  } else {
+    // Merge of the W ranges: every wave's O, max and sum to LDS (the first
+    // barrier: no wave reads Q from there any more), then each thread of the
+    // pair's waves sums pieces of 4 dimensions with weights 2^(m_k - M).
+    float(*so)[kCols][kRow] = reinterpret_cast<float(*)[kCols][kRow]>(lds);
+    __syncthreads();
+    if (col_valid) {
 #pragma unroll
       for (int dt = 0; dt < kDt; ++dt)
 #pragma unroll
         for (int g4 = 0; g4 < 4; ++g4) {
           const f32x4 v = {o[dt][g4 * 4], o[dt][g4 * 4 + 1], o[dt][g4 * 4 + 2], o[dt][g4 * 4 + 3]};
-          *(f32x4*)(po + size_t(n) * D + dt * 32 + g4 * 8 + hh * 4) = v;
+          *(f32x4*)&so[wave][n][dt * 32 + g4 * 8 + hh * 4] = v;
         }
       if (hh == 0) {
-        part_ml[slot * 2] = m_run;
-        part_ml[slot * 2 + 1] = l_tot;
+        s_m[wave][n] = m_run;
+        s_l[wave][n] = l_tot;
       }
     }
-    return;
-  }
-  if (col_valid) {
-    const float inv = 1.f / l_tot;
-    uint16_t* orow = out + qrow;
+    __syncthreads();
+    if (!valid) return;
+    const int w0 = wave / W * W;  // first wave of the pair
+    for (int u = (wave - w0) * 64 + lane; u < n_cols * (D / 4); u += W * 64) {
+      const int c = u / (D / 4), d = u % (D / 4) * 4;
+      float mx = s_m[w0][c];
 #pragma unroll
-    for (int dt = 0; dt < kDt; ++dt)
+      for (int k = 1; k < W; ++k) mx = fmaxf(mx, s_m[w0 + k][c]);
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+      float den = 0.f;
 #pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
+      for (int k = 0; k < W; ++k) {
+        const float m = s_m[w0 + k][c];
+        // (a range that saw no key of this column has m = -inf and weight 0)
+        const float wgt = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - mx);
+        den += wgt * s_l[w0 + k][c];
+        const f32x4 v = *(const f32x4*)&so[w0 + k][c][d];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] += wgt * v[e];
+      }
+      if (n_split > 1) {
+        const size_t slot = (size_t(pair) * n_split + sp) * size_t(cols_cap) + c;
+        *(f32x4*)(part_o + slot * D + d) = acc;
+        if (d == 0) {
+          part_ml[slot * 2] = mx;
+          part_ml[slot * 2 + 1] = den;
+        }
+      } else {
+        const int t = (col0 + c) / G;
+        const float inv = 1.f / den;
         bf16x4 v;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = (__bf16)(o[dt][g4 * 4 + e] * inv);
-        *(bf16x4*)(orow + dt * 32 + g4 * 8 + hh * 4) = v;
+        for (int e = 0; e < 4; ++e) v[e] = (__bf16)(acc[e] * inv);
+        *(bf16x4*)(out + (size_t(q0 + t) * Hq + size_t(h) * G + (col0 + c - t * G)) * D + d) = v;
       }
+    }
   }
 }
 
@@ -296,8 +380,10 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void decode_attn_kernel(
 // dimensions l * D/64 .. of O.  Split 0 holds key 0, visible to every
 // column, so M is finite; a split that saw no visible key has m = -inf,
 // O = 0 and weight 0.
+constexpr int kCombineWaves = 4;  // per workgroup
+
 template <int D>
-__global__ __launch_bounds__(64 * kWavesPerGroup) void decode_combine_kernel(
+__global__ __launch_bounds__(64 * kCombineWaves) void decode_combine_kernel(
     const float* __restrict__ part_o, const float* __restrict__ part_ml, const int32_t* __restrict__ cu_q,
     const int32_t* __restrict__ seq_lens,
     int max_blocks, int n_req, int max_q_len, int Hq, int Hkv, int n_split, int cols_cap,
@@ -305,7 +391,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup) void decode_combine_kernel(
   constexpr int kPer = D / 64;  // dimensions per lane
   typedef float vec_t __attribute__((ext_vector_type(kPer)));
   const int lane = threadIdx.x & 63;
-  const int64_t w = int64_t(blockIdx.x) * kWavesPerGroup + (threadIdx.x >> 6);
+  const int64_t w = int64_t(blockIdx.x) * kCombineWaves + (threadIdx.x >> 6);
   const int c = int(w % cols_cap);
   const int pair = int(w / cols_cap);
   if (pair >= n_req * Hkv) return;
@@ -362,35 +448,79 @@ size_t decode_split_bytes(int B, int max_q_len, int Hq, int Hkv, int D, int n_sp
   return n_split > 1 ? size_t(B) * Hkv * n_split * cols * (D + 2) * sizeof(float) : 0;
 }
 
+// Key ranges (workgroups) a pair is cut into when the choice is automatic, W of
+// a pair's waves being 8: with up to 16 steps a wave one workgroup is faster
+// than two and their merge.
+static int auto_groups(int64_t pairs, int64_t steps, int n_max) {
+  const int64_t n = (steps + 127) / 128;
+  return int(std::max<int64_t>(1, std::min({n, int64_t(n_max), kFill / (8 * pairs)})));
+}
+
 int launch_decode_attn(const uint16_t* q, const uint16_t* k_pool, const uint16_t* v_pool, int num_blocks,
                        const int32_t* block_tables, int max_blocks, const int32_t* cu_q,
                        const int32_t* seq_lens, int B, int max_q_len, int Hq, int Hkv, int D,
-                       float scale_log2, uint16_t* out, int n_split, float* part, void* stream_ptr) {
+                       float scale_log2, uint16_t* out, int n_split, bool automatic, float* part,
+                       void* stream_ptr) {
   hipStream_t stream = static_cast<hipStream_t>(stream_ptr);
-  if (n_split < 1 || n_split > kMaxSplit || (n_split > 1 && !part))
+  const int64_t all_cols = int64_t(max_q_len) * (Hq / Hkv);
+  const int64_t n_ct = (all_cols + 31) / 32;
+  if (n_split < 1 || n_split > kMaxSplit || (n_split > 1 && n_ct > 1))
     return set_error(ILPC_EINVAL, "decode attention: bad split");
-  const int cols_cap = int(std::min<int64_t>(int64_t(max_q_len) * (Hq / Hkv), 32));
+  const int cols_cap = int(std::min<int64_t>(all_cols, 32));
+  // The chip holds kFill waves of this kernel (two per SIMD).  Pairs (column
+  // tiles of them) that give fewer are shared by up to eight waves of a
+  // workgroup, as far as the steps of the longest context allow: their merge
+  // inside the workgroup costs about 1 us, the second launch that merges
+  // workgroups' partials about 5.  us a decode step with its append, before ->
+  // after: 36 requests x 1000 keys, 8 kv heads 47 -> 42; 191 x 1000 (64 q
+  // heads) 147 -> 135; 100 x 2400 (4 kv heads, D 64) 67 -> 55.
+  const int64_t pairs = int64_t(B) * Hkv * n_ct;
+  const int64_t steps = (int64_t(max_blocks) * kBlock + kStepKeys - 1) / kStepKeys;
+  // The doubling stops where the chip is full -- at eight waves a pair a
+  // workgroup is alone on its CU, so that more than 256 would run in two
+  // rounds -- or, on long contexts, three quarters full: those run at the rate
+  // of their reads, and the finer pieces even out the CUs' shares.
+  int w = 1;
+  while (w < 8 && steps >= 2 * w &&
+         (pairs * w * 2 <= kFill || (w < 4 && steps >= 32 && pairs * w * 4 <= kFill * 3)))
+    w *= 2;
+  if (automatic) {
+    n_split = n_split > 1 && w == 8 ? auto_groups(pairs, steps, n_split) : 1;
+  } else if (n_split > 1) {
+    while (w < 8 && w < n_split) w *= 2;
+    n_split = (n_split + w - 1) / w;
+  }
+  if (n_split > 1 && !part) return set_error(ILPC_EINVAL, "decode attention: no room for partial results");
   float* part_ml = part ? part + size_t(B) * Hkv * n_split * cols_cap * D : nullptr;
-  const int64_t items = int64_t(B) * Hkv * n_split;
-  const int64_t groups = (items + kWavesPerGroup - 1) / kWavesPerGroup;
-  if (groups > (int64_t(1) << 31) - 1) return set_error(ILPC_EUNSUP, "decode attention: batch too large");
-  const dim3 grid{unsigned(groups)}, block{64 * kWavesPerGroup};
-  if (D == 128)
-    hipLaunchKernelGGL(decode_attn_kernel<128>, grid, block, 0, stream, q, k_pool, v_pool, num_blocks,
-                       block_tables, max_blocks, cu_q, seq_lens, B, max_q_len, Hq, Hkv, scale_log2, out,
-                       n_split, cols_cap, part, part_ml);
-  else
-    hipLaunchKernelGGL(decode_attn_kernel<64>, grid, block, 0, stream, q, k_pool, v_pool, num_blocks,
-                       block_tables, max_blocks, cu_q, seq_lens, B, max_q_len, Hq, Hkv, scale_log2, out,
-                       n_split, cols_cap, part, part_ml);
+  const int64_t items = pairs * n_split, per_group = group_waves(w) / w;
+  const int64_t groups = (items + per_group - 1) / per_group;
+  if (items > INT32_MAX) return set_error(ILPC_EUNSUP, "decode attention: batch too large");
+  const dim3 grid{unsigned(groups)}, block{unsigned(64 * group_waves(w))};
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, block, 0, stream, q, k_pool, v_pool, num_blocks, block_tables, max_blocks,
+                       cu_q, seq_lens, B, max_q_len, Hq, Hkv, scale_log2, out, int(n_ct), n_split, cols_cap, part,
+                       part_ml);
+  };
+  if (D == 128) {
+    if (w == 1) launch(decode_attn_kernel<128, 1>);
+    else if (w == 2) launch(decode_attn_kernel<128, 2>);
+    else if (w == 4) launch(decode_attn_kernel<128, 4>);
+    else launch(decode_attn_kernel<128, 8>);
+  } else {
+    if (w == 1) launch(decode_attn_kernel<64, 1>);
+    else if (w == 2) launch(decode_attn_kernel<64, 2>);
+    else if (w == 4) launch(decode_attn_kernel<64, 4>);
+    else launch(decode_attn_kernel<64, 8>);
+  }
   hipError_t e = hipGetLastError();
   if (e == hipSuccess && n_split > 1) {
-    const dim3 cgrid{unsigned((int64_t(B) * Hkv * cols_cap + kWavesPerGroup - 1) / kWavesPerGroup)};
+    const dim3 cgrid{unsigned((int64_t(B) * Hkv * cols_cap + kCombineWaves - 1) / kCombineWaves)};
+    const dim3 cblock{64 * kCombineWaves};
     if (D == 128)
-      hipLaunchKernelGGL(decode_combine_kernel<128>, cgrid, block, 0, stream, part, part_ml, cu_q, seq_lens,
+      hipLaunchKernelGGL(decode_combine_kernel<128>, cgrid, cblock, 0, stream, part, part_ml, cu_q, seq_lens,
                          max_blocks, B, max_q_len, Hq, Hkv, n_split, cols_cap, out);
     else
-      hipLaunchKernelGGL(decode_combine_kernel<64>, cgrid, block, 0, stream, part, part_ml, cu_q, seq_lens,
+      hipLaunchKernelGGL(decode_combine_kernel<64>, cgrid, cblock, 0, stream, part, part_ml, cu_q, seq_lens,
                          max_blocks, B, max_q_len, Hq, Hkv, n_split, cols_cap, out);
     e = hipGetLastError();
   }

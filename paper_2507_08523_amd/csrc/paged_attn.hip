@@ -1116,6 +1116,18 @@ int decode_auto_split(int64_t B, int64_t Hkv, int64_t max_blocks) {
 
 bool decode_shaped(int64_t max_q_len, int Hq, int Hkv) { return max_q_len * (Hq / Hkv) <= kDecodeCols; }
 
+// Few query columns over long contexts: at most kFewTiles column tiles of 32
+// in the whole batch.  The persistent kernel would put them on a few CUs, each
+// running through all the keys; the decode kernel cuts the keys of a tile over
+// four or eight waves.
+constexpr int64_t kFewTiles = 512;
+constexpr int64_t kFewMinKeys = 1024;  // context bound 16 * max_blocks
+
+bool few_columns(int64_t B, int64_t max_q_len, int Hq, int Hkv, int64_t max_blocks) {
+  const int64_t tiles = B * Hkv * ((max_q_len * (Hq / Hkv) + kDecodeCols - 1) / kDecodeCols);
+  return tiles <= kFewTiles && max_blocks * kBlock >= kFewMinKeys;
+}
+
 }  // namespace
 
 extern "C" int ilpc_attn_workspace_bytes(int32_t B, int32_t max_q_len, int32_t Hq, int32_t Hkv,
@@ -1217,25 +1229,28 @@ extern "C" int ilpc_paged_prefill_attn(const uint16_t* q, const uint16_t* k_pool
   if (!workspace || workspace_bytes < kQueueWords * sizeof(unsigned) || !aligned16(workspace))
     return ilpc::set_error(ILPC_EINVAL, "%s: workspace must be %zu bytes, 16-byte aligned", fn,
                            kQueueWords * sizeof(unsigned));
-  // Decode-shaped batches go to the one-wave-per-pair kernel: split into key
-  // ranges when the pairs are fewer than the SIMDs and the workspace has room
-  // for the partials (after the queue counters), unsplit when the pairs at
-  // least fill the compute units.
+  // Decode-shaped batches go to the decode kernel: split into key ranges when
+  // the pairs are fewer than the SIMDs and the workspace has room for the
+  // partials (after the queue counters), else unsplit when the pairs at least
+  // fill the compute units.
+  const float scale_log2 = softmax_scale * 1.4426950408889634f;
   if (decode_shaped(max_q_len, Hq, Hkv)) {
-    const float scale_log2 = softmax_scale * 1.4426950408889634f;
     const int n_split = decode_auto_split(B, Hkv, max_blocks);
     const size_t head = kQueueWords * sizeof(unsigned);
     if (n_split > 1 && workspace_bytes >= head + ilpc::decode_split_bytes(B, max_q_len, Hq, Hkv, D, n_split))
       return ilpc::launch_decode_attn(q, k_pool, v_pool, num_blocks, block_tables, max_blocks, cu_q, seq_lens,
-                                      B, max_q_len, Hq, Hkv, D, scale_log2, out, n_split,
+                                      B, max_q_len, Hq, Hkv, D, scale_log2, out, n_split, true,
                                       reinterpret_cast<float*>(static_cast<uint8_t*>(workspace) + head), stream);
     if (int64_t(B) * Hkv >= device_cus())
       return ilpc::launch_decode_attn(q, k_pool, v_pool, num_blocks, block_tables, max_blocks, cu_q, seq_lens,
-                                      B, max_q_len, Hq, Hkv, D, scale_log2, out, 1, nullptr, stream);
+                                      B, max_q_len, Hq, Hkv, D, scale_log2, out, 1, true, nullptr, stream);
+  } else if (few_columns(B, max_q_len, Hq, Hkv, max_blocks)) {
+    return ilpc::launch_decode_attn(q, k_pool, v_pool, num_blocks, block_tables, max_blocks, cu_q, seq_lens, B,
+                                    max_q_len, Hq, Hkv, D, scale_log2, out, 1, true, nullptr, stream);
   }
   const int64_t col_tiles = (int64_t(max_q_len) * (Hq / Hkv) + kCols - 1) / kCols;
   return launch_attn<kFull>(fn, q, k_pool, v_pool, num_blocks, block_tables, max_blocks, cu_q, seq_lens, B,
-                            Hq, Hkv, D, col_tiles, softmax_scale * 1.4426950408889634f, out,
+                            Hq, Hkv, D, col_tiles, scale_log2, out,
                             static_cast<unsigned*>(workspace), 0, nullptr, nullptr, 0,
                             static_cast<hipStream_t>(stream));
 }
@@ -1272,7 +1287,8 @@ extern "C" int ilpc_paged_decode_attn(const uint16_t* q, const uint16_t* k_pool,
                            (long long)max_q_len * (Hq / Hkv), kDecodeCols);
   if (n_split < 0 || n_split > ilpc::kMaxSplit)
     return ilpc::set_error(ILPC_EINVAL, "%s: n_split %d outside [0, %d]", fn, n_split, ilpc::kMaxSplit);
-  if (n_split == 0) n_split = decode_auto_split(B, Hkv, max_blocks);
+  const bool automatic = n_split == 0;
+  if (automatic) n_split = decode_auto_split(B, Hkv, max_blocks);
   if (int64_t(B) * Hkv * n_split > INT32_MAX)
     return ilpc::set_error(ILPC_EUNSUP, "%s: B * Hkv * n_split too large", fn);
   const size_t need = ilpc::decode_split_bytes(B, max_q_len, Hq, Hkv, D, n_split);
@@ -1281,7 +1297,7 @@ extern "C" int ilpc_paged_decode_attn(const uint16_t* q, const uint16_t* k_pool,
                            n_split, need);
   return ilpc::launch_decode_attn(q, k_pool, v_pool, num_blocks, block_tables, max_blocks, cu_q, seq_lens, B,
                                   max_q_len, Hq, Hkv, D, softmax_scale * 1.4426950408889634f, out, n_split,
-                                  static_cast<float*>(workspace), stream);
+                                  automatic, static_cast<float*>(workspace), stream);
 }
 
 extern "C" int ilpc_attn_cascade_workspace_bytes(int32_t B, int32_t max_q_len, int32_t Hq, int32_t Hkv,
@@ -1320,6 +1336,11 @@ extern "C" int ilpc_paged_prefill_attn_cascade(
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int G = Hq / Hkv;
   const int64_t col_tiles = (int64_t(max_q_len) * G + kCols - 1) / kCols;
+  // (few_columns() as in ilpc_paged_prefill_attn, whose pass shared_len = 0 runs;
+  // with so few columns the sharing saves less than the idle CUs cost)
+  if (!decode_shaped(max_q_len, Hq, Hkv) && few_columns(B, max_q_len, Hq, Hkv, max_blocks))
+    return ilpc::launch_decode_attn(q, k_pool, v_pool, num_blocks, block_tables, max_blocks, cu_q, seq_lens, B,
+                                    max_q_len, Hq, Hkv, D, scale_log2, out, 1, true, nullptr, stream);
   if (shared_len == 0)
     return launch_attn<kFull>(fn, q, k_pool, v_pool, num_blocks, block_tables, max_blocks, cu_q, seq_lens,
                               B, Hq, Hkv, D, col_tiles, scale_log2, out, queue_shared, 0, nullptr, nullptr,

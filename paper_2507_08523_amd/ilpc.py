@@ -508,9 +508,8 @@ def paged_decode_attn(q, k_pool, v_pool, block_tables, cu_q, seq_lens, max_q_len
             _dev(block_tables, torch.int32, "block_tables", 2), block_tables.shape[1],
             _dev(cu_q, torch.int32, "cu_q", 1), _dev(seq_lens, torch.int32, "seq_lens", 1), B,
             int(max_q_len), Hq, Hkv, D, bs, float(scale), _dev(out, torch.bfloat16, "out", 3))
-    if n_split == 0:
-        n_split = decode_split(B, Hkv, block_tables.shape[1])
-    need = decode_workspace_bytes(B, int(max_q_len), Hq, Hkv, D, n_split) if n_split >= 1 else 0
+    room = n_split if n_split != 0 else decode_split(B, Hkv, block_tables.shape[1])
+    need = decode_workspace_bytes(B, int(max_q_len), Hq, Hkv, D, room) if room >= 1 else 0
     if workspace is None and need:
         workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
     ws_ptr, ws_bytes = (None, 0) if workspace is None else (_dev(workspace, torch.uint8, "workspace", 1),

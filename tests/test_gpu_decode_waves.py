@@ -1,0 +1,107 @@
+"""Decode attention with several waves to a (request, kv head) pair: every way
+the pairs are dealt to waves and workgroups (one to eight waves a pair, with and
+without a second launch), contexts from one key up, ragged, with requests that
+have no query, and several column tiles a pair; against float64.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2507_08523_amd import ilpc
+
+pytestmark = pytest.mark.gpu
+
+BLOCK = 16
+
+
+@pytest.mark.parametrize("D,Hq,Hkv,B,L_max,rows,n_split", [
+    (128, 8, 8, 300, 100, 1, 1),     # 2400 pairs: one wave each
+    (128, 32, 8, 131, 70, 1, 1),     # 1048 pairs: two waves each
+    (128, 64, 8, 33, 300, 1, 1),     # four
+    (128, 28, 4, 9, 33, 4, 1),       # 2 steps: two waves, 28 columns
+    (64, 32, 2, 5, 20, 2, 1),        # 1 step, 32 columns: one wave
+    (64, 12, 4, 70, 500, 1, 1),
+    (128, 8, 8, 5, 200, 3, 2),       # 2 to 4 ranges: one workgroup a pair, no second launch
+    (128, 32, 8, 5, 200, 1, 4),
+    (128, 32, 8, 5, 400, 2, 5),      # a second launch, uneven
+    (64, 16, 2, 3, 1000, 4, 64),
+    (128, 32, 8, 5, 400, 2, 20),     # three workgroups a pair
+    (128, 64, 8, 6, 2100, 1, 0),     # the library's choice: one workgroup a pair
+    (128, 8, 2, 2, 9000, 1, 0),      # several, and a second launch
+])
+def test_waves_per_pair(D, Hq, Hkv, B, L_max, rows, n_split):
+    def call(q, k_pool, v_pool, tables, cu, L, scale, out):
+        ilpc.paged_decode_attn(q, k_pool, v_pool, tables, cu, L, rows, scale, out, n_split=n_split)
+
+    _check(D, Hq, Hkv, B, L_max, rows, call)
+
+
+@pytest.mark.parametrize("D,Hq,Hkv,B,L_max,rows", [
+    (128, 64, 8, 1, 1111, 64),       # 128 column tiles of 32: eight waves each
+    (128, 28, 4, 3, 1030, 37),       # ragged group of 7, partial tiles
+    (128, 8, 8, 2, 1500, 33),        # one head a group: a tile of 32 rows, then one of 1
+    (64, 32, 2, 4, 1024, 61),        # the shortest context bound of this path, 248 tiles
+    (128, 32, 8, 4, 1040, 128),      # 512 tiles, the most: four waves each
+    (128, 32, 8, 4, 1040, 129),      # 544: the persistent kernel
+    (64, 64, 1, 5, 1200, 3),         # 64 heads a group: two tiles a row
+])
+def test_few_columns_over_long_contexts(D, Hq, Hkv, B, L_max, rows):
+    """Small prefills through the prefill entry (64 bytes of workspace) and, bit
+    for bit the same, through the shared-prefix entry."""
+    outs = []
+
+    def call(q, k_pool, v_pool, tables, cu, L, scale, out):
+        ws = torch.zeros(64, dtype=torch.uint8, device="cuda")
+        ilpc.paged_prefill_attn(q, k_pool, v_pool, tables, cu, L, rows, scale, out, ws)
+        need = ilpc.attn_cascade_workspace_bytes(B, rows, Hq, Hkv, D)
+        cws = torch.zeros(need, dtype=torch.uint8, device="cuda")
+        other = torch.full_like(out, float("nan"))
+        ilpc.paged_prefill_attn_cascade(q, k_pool, v_pool, tables, cu, L, rows, 0, scale, other, cws)
+        outs.extend([out, other])
+
+    _check(D, Hq, Hkv, B, L_max, rows, call)
+    assert torch.equal(outs[0], outs[1])
+
+
+def _check(D, Hq, Hkv, B, L_max, rows, call):
+    rng = np.random.default_rng(B + L_max)
+    q_len = rng.integers(1, rows + 1, B)
+    q_len[rng.random(B) < 0.1] = 0
+    q_len[0] = rows
+    L = np.maximum(rng.integers(1, L_max + 1, B), q_len).astype(np.int32)
+    L[-1] = L_max
+    mb, NB, G = -(-L_max // BLOCK), 64, Hq // Hkv
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(B)
+
+    def randn(*shape):
+        return torch.randn(shape, generator=gen, device="cuda", dtype=torch.bfloat16)
+
+    k_pool, v_pool = randn(NB, Hkv, BLOCK, D), randn(NB, Hkv, D, BLOCK)
+    tables = rng.integers(0, NB, (B, mb)).astype(np.int32)
+    cu = np.zeros(B + 1, np.int32)
+    cu[1:] = np.cumsum(q_len)
+    q = randn(int(cu[-1]), Hq, D)
+    got = torch.full_like(q, float("nan"))
+    call(q, k_pool, v_pool, torch.from_numpy(tables).cuda(), torch.from_numpy(cu).cuda(),
+         torch.from_numpy(L).cuda(), D ** -0.5, got)
+    torch.cuda.synchronize()
+    got, qd, kd, vd = (x.double().cpu().numpy() for x in (got.float(), q.float(), k_pool.float(), v_pool.float()))
+    worst = 0.0
+    for r in range(B):
+        n = int(q_len[r])
+        ids = tables[r, np.arange(int(L[r])) // BLOCK]
+        slot = np.arange(int(L[r])) % BLOCK
+        for h in range(Hkv):
+            k, v = kd[ids, h, slot], vd[ids, h, :, slot]                  # [L, D]
+            sc = qd[cu[r]:cu[r + 1], h * G:(h + 1) * G] @ k.T * D ** -0.5  # [n, G, L]
+            vis = int(L[r]) - n + np.arange(n) + 1
+            sc[np.broadcast_to((np.arange(int(L[r]))[None, :] >= vis[:, None])[:, None, :], sc.shape)] = -np.inf
+            if not n:
+                continue
+            p = np.exp(sc - sc.max(axis=2, keepdims=True))
+            ref = p @ v / p.sum(axis=2, keepdims=True)
+            worst = max(worst, float(np.abs(got[cu[r]:cu[r + 1], h * G:(h + 1) * G] - ref).max()))
+    # |V| reaches about 4.5; the probabilities (sum 1) and the output each round
+    # to bf16 once (2^-9 relative), so 4.5 * 2^-8 = 1.8e-2 bounds the error
+    assert worst <= 2e-2, worst
