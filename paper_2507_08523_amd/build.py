@@ -1,4 +1,5 @@
-"""Builds libilpc.so (host prefix cache + gfx950 kernels) in-tree with hipcc.
+"""Builds libilpc.so (host prefix cache + gfx950 kernels) in-tree with hipcc, and
+the native part of the Python binding (_binding.so) against PyTorch's headers.
 
     python -m paper_2507_08523_amd.build
 
@@ -20,6 +21,8 @@ SOURCES = [os.path.join(PKG, "csrc", "prefix_cache.cpp"), os.path.join(PKG, "csr
            os.path.join(PKG, "csrc", "paged_attn.hip"), os.path.join(PKG, "csrc", "rope_append.hip"),
            os.path.join(PKG, "csrc", "decode_attn.hip"),
            os.path.join(PKG, "csrc", "attn_noalloc.hip")]
+BINDING = os.path.join(PKG, "_binding.so")
+BINDING_SOURCE = os.path.join(PKG, "csrc", "binding.cpp")
 ARCH = "gfx950"
 
 
@@ -28,8 +31,39 @@ def hipcc() -> str:
     return os.path.join(rocm, "bin", "hipcc")
 
 
+def build_binding(verbose: bool = False) -> str:
+    """Compile the native binding (host code only) against the torch that is installed (nothing
+    without a HIP build of torch: no tensor is on a GPU then)."""
+    import sysconfig
+
+    try:
+        import torch
+    except ImportError:
+        return ""
+    if torch.version.hip is None:
+        return ""
+
+    t = os.path.dirname(torch.__file__)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    tmp = BINDING + ".tmp"
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-isystem", os.path.join(t, "include"),
+           "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
+           "-isystem", os.path.join(rocm, "include"), "-isystem", sysconfig.get_paths()["include"],
+           BINDING_SOURCE, "-L", os.path.join(t, "lib"), "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10",
+           "-lc10_hip", "-o", tmp]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("binding.cpp failed:\n" + res.stdout + res.stderr)
+    if verbose and (res.stdout or res.stderr):
+        print(res.stdout + res.stderr, file=sys.stderr)
+    os.replace(tmp, BINDING)
+    return BINDING
+
+
 def build(verbose: bool = False) -> str:
-    """Compile the library (always recompiles) and return its path."""
+    """Compile the library and the binding (always recompiles) and return the library's path."""
     tmp = LIB + ".tmp"
     cmd = [hipcc(), f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-shared",
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -43,6 +77,7 @@ def build(verbose: bool = False) -> str:
     if verbose and msgs:
         print("\n".join(msgs), file=sys.stderr)
     os.replace(tmp, LIB)
+    build_binding(verbose)
     return LIB
 
 

@@ -1,4 +1,5 @@
-"""ctypes binding of libilpc.so (C ABI in include/ilpc.h).
+"""Binding of libilpc.so (C ABI in include/ilpc.h): ctypes, and natively
+(csrc/binding.cpp) the device calls a serving loop issues per layer.
 
 Argument marshalling only: every step of the path runs in the library (host
 C++ prefix matching, HIP kernels for K/V append and attention).  Loading fails
@@ -71,6 +72,7 @@ _SIGS = [
 SYMBOLS = [s[0] for s in _SIGS]
 
 _lib = None
+_binding = None
 
 
 class ILPCError(RuntimeError):
@@ -92,6 +94,35 @@ def load():
             fn.argtypes = args
         _lib = lib
     return _lib
+
+
+class _NoNative:
+    """Stands in for the native binding where torch knows no GPU: takes no call."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+def _native():
+    """The native part of the binding, bound to the loaded library; raises if it has not been built."""
+    global _binding
+    if _binding is None:
+        import torch
+
+        lib = load()
+        if torch.version.hip is None:
+            _binding = _NoNative()
+            return _binding
+        try:
+            from . import _binding as mod
+        except ImportError as e:
+            raise ILPCError(EINVAL, f"the native binding cannot be loaded ({e}): run "
+                                    f"`python -m paper_2507_08523_amd.build`") from e
+        mod.bind(*(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in (
+            "ilpc_kv_append", "ilpc_rope_kv_append", "ilpc_attn_workspace_bytes", "ilpc_paged_prefill_attn",
+            "ilpc_paged_prefill_attn_cascade")))
+        _binding = mod
+    return _binding
 
 
 def _check(rc: int):
@@ -327,6 +358,12 @@ def kv_append(k_new, v_new, k_pool, v_pool, block_tables, cu_new, start_pos, max
     """Write packed new K/V rows [total, Hkv, D] into the pools (async on the stream)."""
     import torch
 
+    # (here and below) the whole call natively; None: not a call it takes as it stands
+    rc = (_binding or _native()).kv_append(k_new, v_new, k_pool, v_pool, block_tables, cu_new, start_pos, max_new,
+                                         stream)
+    if rc is not None:
+        return _check(rc)
+
     NB, Hkv, bs, D = k_pool.shape
     if v_pool.shape != (NB, Hkv, D, bs) or k_new.shape[1:] != (Hkv, D) or v_new.shape != k_new.shape:
         raise ILPCError(EINVAL, "kv_append: inconsistent K/V/pool shapes")
@@ -348,6 +385,11 @@ def rope_kv_append(q, q_out, k_new, v_new, k_pool, v_pool, block_tables, cu_new,
     q, q_out: [total, Hq, D] bf16 or both None (q_out may be q); inv_freq: fp32 [D/2].
     """
     import torch
+
+    rc = (_binding or _native()).rope_kv_append(q, q_out, k_new, v_new, k_pool, v_pool, block_tables, cu_new,
+                                              start_pos, max_new, inv_freq, stream)
+    if rc is not None:
+        return _check(rc)
 
     NB, Hkv, bs, D = k_pool.shape
     if v_pool.shape != (NB, Hkv, D, bs) or k_new.shape[1:] != (Hkv, D) or v_new.shape != k_new.shape:
@@ -421,6 +463,11 @@ def paged_prefill_attn(q, k_pool, v_pool, block_tables, cu_q, seq_lens, max_q_le
     split each pair's keys over several waves).
     """
     import torch
+
+    rc = (_binding or _native()).paged_prefill_attn(q, k_pool, v_pool, block_tables, cu_q, seq_lens, max_q_len, scale,
+                                                  out, workspace, stream, _workspaces)
+    if rc is not None:
+        return _check(rc)
 
     NB, Hkv, bs, D = k_pool.shape
     total, Hq, Dq = q.shape
@@ -531,6 +578,11 @@ def paged_prefill_attn_cascade(q, k_pool, v_pool, block_tables, cu_q, seq_lens, 
     bytes whose first 128 bytes are zero before the first call.
     """
     import torch
+
+    rc = (_binding or _native()).paged_prefill_attn_cascade(q, k_pool, v_pool, block_tables, cu_q, seq_lens, max_q_len,
+                                                          shared_len, scale, out, workspace, stream)
+    if rc is not None:
+        return _check(rc)
 
     NB, Hkv, bs, D = k_pool.shape
     total, Hq, Dq = q.shape
