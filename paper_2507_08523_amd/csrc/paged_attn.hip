@@ -216,11 +216,11 @@ __global__ __launch_bounds__(256) void kv_append_kernel(
 // paged attention.  Work items are (column tile, kv head, request) triples,
 // numbered request-major with the heaviest column tile of a (request, kv head)
 // first.  The kernel is persistent: two workgroups per CU take items from
-// eight queues, one per XCD, each holding a contiguous range of item numbers
+// eight queues, one per XCD, each holding whole runs of item numbers
 // so that the items sharing one (request, kv head) -- and so the same K/V
-// blocks -- are worked on under one XCD's L2.  A workgroup drains the queue
-// of its own XCD first, then helps the others.  The queue counters live in
-// the caller's workspace; the last workgroup to finish clears them again.
+// blocks -- are worked on under one XCD's L2.  The queue counters live in the
+// caller's workspace and are zero again when a launch ends (the hand-out is
+// described in the kernel).
 constexpr int kMaxTableBlocks = 1 << 24;  // block-table width accepted (keeps token positions in int)
 // Largest per-lane sum of a tile's exponentials accepted without taking the
 // tile's column max (each exponential is then at most this, 2^8).
@@ -1347,7 +1347,7 @@ extern "C" int ilpc_paged_prefill_attn_cascade(
                               0, s);
   // One launch (kFused) for prefill-shaped batches whose shared prefix holds
   // at least three 64-key tiles and whose per-item tile list fits: at most
-  // 256 / G + 1 requests have rows in an item, each with at most
+  // 128 / G + 1 requests have rows in an item, each with at most
   // ceil(16 * max_blocks / 64) - T_s tiles of its own.
   const int64_t T_s = shared_len / kKeys;
   const int64_t own_tiles = std::max<int64_t>(0, (int64_t(max_blocks) * kBlock + kKeys - 1) / kKeys - T_s);
