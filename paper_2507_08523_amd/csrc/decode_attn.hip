@@ -448,12 +448,22 @@ size_t decode_split_bytes(int B, int max_q_len, int Hq, int Hkv, int D, int n_sp
   return n_split > 1 ? size_t(B) * Hkv * n_split * cols * (D + 2) * sizeof(float) : 0;
 }
 
-// Key ranges (workgroups) a pair is cut into when the choice is automatic, W of
-// a pair's waves being 8: with up to 16 steps a wave one workgroup is faster
-// than two and their merge.
+// Key ranges (workgroups of 8 waves) a pair is cut into when the choice is
+// automatic.  A wave's key steps follow each other at 1.8 us each (a load's
+// round trip; D = 64: 1), where the second launch that merges the workgroups'
+// partials costs 2 to 4 us, so from 32 steps on a pair gets up to one
+// workgroup per 8 steps (a step or two a wave), as far as a workgroup per CU
+// goes round; below three workgroups (over 85 pairs) the reads are the bound,
+// and the merge pays only past 128 steps.  us per launch, one workgroup ->
+// this rule, 8 kv heads, D 128 (D 64 with 2 kv heads): 4 requests of 1000 keys
+// 14.2 -> 10.4 (8.8 -> 8.2), of 2100 24.9 -> 14.3 (13.7 -> 9.5), of 4000
+// 41.5 -> 18.4 (21.9 -> 9.5); 8 of 2100 25.8 -> 19.0; against it, 4 of 604
+// 10.9 -> 10.2 (7.1 -> 8.1) and 16 of 2100 26.7 -> 29.0, which stay at one.
 static int auto_groups(int64_t pairs, int64_t steps, int n_max) {
-  const int64_t n = (steps + 127) / 128;
-  return int(std::max<int64_t>(1, std::min({n, int64_t(n_max), kFill / (8 * pairs)})));
+  const int64_t room = kFill / (8 * pairs);
+  int64_t n = (steps + 127) / 128;
+  if (steps >= 32 && room >= 3) n = std::max(n, std::min<int64_t>(steps / 8, 8));
+  return int(std::max<int64_t>(1, std::min({n, int64_t(n_max), room})));
 }
 
 int launch_decode_attn(const uint16_t* q, const uint16_t* k_pool, const uint16_t* v_pool, int num_blocks,

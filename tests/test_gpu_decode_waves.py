@@ -63,6 +63,29 @@ def test_few_columns_over_long_contexts(D, Hq, Hkv, B, L_max, rows):
     assert torch.equal(outs[0], outs[1])
 
 
+@pytest.mark.parametrize("D,Hq,Hkv,B,L_max,rows", [
+    (128, 64, 8, 4, 992, 1),         # 31 steps: one workgroup a pair
+    (128, 64, 8, 4, 993, 1),         # 32: four of them
+    (64, 16, 2, 1, 1300, 4),         # 41 steps in five, some ranges past the shorter rows' last key
+    (128, 28, 4, 8, 2047, 1),        # 32 pairs: the most, eight
+    (128, 5, 5, 17, 1100, 1),        # 85 pairs: three
+    (128, 4, 2, 43, 1100, 1),        # 86: one
+])
+def test_library_choice_of_ranges(D, Hq, Hkv, B, L_max, rows):
+    """The automatic choice, through the decode entry and, bit for bit the same, the prefill entry."""
+    outs = []
+
+    def call(q, k_pool, v_pool, tables, cu, L, scale, out):
+        ilpc.paged_decode_attn(q, k_pool, v_pool, tables, cu, L, rows, scale, out, n_split=0)
+        ws = torch.zeros(ilpc.attn_workspace_bytes(B, rows, Hq, Hkv, D), dtype=torch.uint8, device="cuda")
+        other = torch.full_like(out, float("nan"))
+        ilpc.paged_prefill_attn(q, k_pool, v_pool, tables, cu, L, rows, scale, other, ws)
+        outs.extend([out, other])
+
+    _check(D, Hq, Hkv, B, L_max, rows, call)
+    assert torch.equal(outs[0], outs[1])
+
+
 def _check(D, Hq, Hkv, B, L_max, rows, call):
     rng = np.random.default_rng(B + L_max)
     q_len = rng.integers(1, rows + 1, B)
