@@ -243,8 +243,9 @@ int ilpc_rope_kv_append(const uint16_t* q, uint16_t* q_out, int32_t Hq, const ui
  * to the cached KV of its whole context): the same operation, arguments,
  * layouts and bounds rules as ilpc_paged_prefill_attn, for batches whose
  * max_q_len * (Hq / Hkv) <= 32 (ILPC_EUNSUP otherwise).  One wave per
- * (request, kv head) pair -- up to eight where the pairs are too few to fill
- * the chip -- streams that request's K/V blocks from the pools;
+ * (request, kv head) pair -- more where the pairs are too few to fill the
+ * chip, each a range of the keys -- streams that request's K/V blocks from the
+ * pools;
  * results agree with ilpc_paged_prefill_attn to the attention tolerance, not
  * bit for bit.  ilpc_paged_prefill_attn takes this path by itself for such
  * batches: split as for n_split = 0 when its workspace has room for
@@ -253,13 +254,14 @@ int ilpc_rope_kv_append(const uint16_t* q, uint16_t* q_out, int32_t Hq, const ui
  * (B * Hkv * ceil(max_q_len * Hq / Hkv / 32) <= 512) over contexts that may
  * reach 1024 keys (16 * max_blocks).
  *
- * n_split      [host] key ranges per pair, 1 .. 64, or 0 for
- *                     the library's choice (at most ilpc_decode_split()).
- *                     With n > 1 the pair's keys are cut into at least n
- *                     ranges, up to eight to a workgroup, which merges them;
- *                     past 8 the workgroups' partial results (fp32) go to the
- *                     workspace and a second kernel merges those, so that
- *                     batches with few pairs still occupy the whole chip.
+ * n_split      [host] key ranges per pair, 1 .. 64, or 0 for the library's
+ *                     choice.  With n > 1 a pair's keys are cut into at least
+ *                     n ranges (or one per 32 keys of the bound
+ *                     16 * max_blocks, if those are fewer), one per wave.  The
+ *                     waves of a workgroup, up to eight, merge theirs; the
+ *                     partial results (fp32) of a pair's workgroups, at most
+ *                     n, go to the workspace and a second kernel merges those.
+ *                     With 1 a pair stays within one workgroup.
  * workspace    [device] >= ilpc_decode_workspace_bytes(..., n) bytes,
  *                     16-byte aligned, no initial contents needed (NULL with
  *                     0 bytes when n = 1).  Calls that may run concurrently

@@ -6,7 +6,7 @@
 // request the work is bound by reading K and V from HBM, not by the matrix
 // cores, so this kernel drops the workgroup-shared LDS ring of the prefill
 // kernel: every wave owns one (request, kv head) -- or, where the batch has too
-// few of these to fill the chip, a range of its keys -- and streams that K
+// few of these to fill the chip, a range of its keys -- and streams its K
 // and V blocks straight from the pools into registers, two 16-token pool
 // blocks (32 keys) per step, with the next step's loads in flight while the
 // current one is computed.  The G query heads of the kv head times the
@@ -40,7 +40,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBlock = 16;
 constexpr int kStepKeys = 32;        // keys per step (two pool blocks)
-constexpr int64_t kFill = 2048;       // waves the chip holds (256 CUs x 4 SIMDs x 2)
+constexpr int kMaxGroups = 16;       // most workgroups a pair's keys are cut over by the library's choice
 constexpr float kLazyRescale = 8.f;  // log2 growth of a column max tolerated before rescaling O
 
 // Key held by MFMA row m of a step: inside every 16 keys the groups [4,8)
@@ -443,27 +443,73 @@ __global__ __launch_bounds__(64 * kCombineWaves) void decode_combine_kernel(
 
 namespace ilpc {
 
+int device_cus() {
+  static int cached[64] = {};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0) return 0;
+  if (dev < 64 && cached[dev] > 0) return cached[dev];
+  int cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+  if (dev < 64) cached[dev] = cus;
+  return cus;
+}
+
 size_t decode_split_bytes(int B, int max_q_len, int Hq, int Hkv, int D, int n_split) {
   const int64_t cols = std::min<int64_t>(int64_t(max_q_len) * (Hq / Hkv), 32);
   return n_split > 1 ? size_t(B) * Hkv * n_split * cols * (D + 2) * sizeof(float) : 0;
 }
 
-// Key ranges (workgroups of 8 waves) a pair is cut into when the choice is
-// automatic.  A wave's key steps follow each other at 1.8 us each (a load's
-// round trip; D = 64: 1), where the second launch that merges the workgroups'
-// partials costs 2 to 4 us, so from 32 steps on a pair gets up to one
-// workgroup per 8 steps (a step or two a wave), as far as a workgroup per CU
-// goes round; below three workgroups (over 85 pairs) the reads are the bound,
-// and the merge pays only past 128 steps.  us per launch, one workgroup ->
-// this rule, 8 kv heads, D 128 (D 64 with 2 kv heads): 4 requests of 1000 keys
-// 14.2 -> 10.4 (8.8 -> 8.2), of 2100 24.9 -> 14.3 (13.7 -> 9.5), of 4000
-// 41.5 -> 18.4 (21.9 -> 9.5); 8 of 2100 25.8 -> 19.0; against it, 4 of 604
-// 10.9 -> 10.2 (7.1 -> 8.1) and 16 of 2100 26.7 -> 29.0, which stay at one.
-static int auto_groups(int64_t pairs, int64_t steps, int n_max) {
-  const int64_t room = kFill / (8 * pairs);
-  int64_t n = (steps + 127) / 128;
-  if (steps >= 32 && room >= 3) n = std::max(n, std::min<int64_t>(steps / 8, 8));
-  return int(std::max<int64_t>(1, std::min({n, int64_t(n_max), room})));
+// How a launch cuts its pairs: waves of a workgroup to a pair (column tile of
+// a pair), and workgroups to a pair (with more than one, a second launch merges
+// their partials).  steps: 32-key steps of the longest context; n_max: room for
+// partials; least: ranges, one per wave, there have to be.
+//
+// A CU takes in about 58 GB/s whatever runs on it (8000 keys, D 128, us: one
+// workgroup of four waves 71.7, of eight 72.3), so what shortens a long context
+// is CUs.  Waves double up to four, one workgroup, as long as every workgroup has
+// a CU to itself: beyond, some CUs get two and the launch waits for them (us, 800
+// keys: 264 pairs by two 20.4, by four 26.0; 576 pairs by one 35.8, by two 46.7,
+// by four 40.0); column tiles of one pair, which read the same keys, take two
+// workgroups to a CU at D = 64 (512 of them, 16 K keys: by two 167, by four 147).
+// Eight gain only at D = 64 where a pair has one workgroup and 24 steps or more
+// (4 requests, 2 kv heads, 16 K keys 86.5 -> 73.8; 64 of 800 8.9 -> 8.2).
+//
+// A wave's steps follow each other at about 1 us (D = 64: 0.55) and the second
+// launch costs 3 to 3.5 us, so workgroups are added -- one to a CU, at most 16 --
+// where they take kGain steps off every wave, and no more of them than keep that
+// step count; below three to a pair (over 85 pairs) the reads are the bound and
+// two pay only past 128 steps.  us, one workgroup -> this rule, 8 kv heads, D 128
+// (D 64 with 2 kv heads): 1 request of 604 keys 9.2 -> 8.5, of 8000 71.7 -> 13.2;
+// 4 of 1000 12.8 -> 8.7 (8.2 -> 7.2), of 2100 22.9 -> 12.4, of 4000 38.5 -> 16.9
+// (22.1 -> 8.3); 8 of 2100 23.4 -> 17.2; 16 of 8000 110.8 -> 95.3; left at one
+// because it loses: 4 of 400 (7.5 -> 8.0), 16 of 2100 (24.5 -> 26.8).
+struct Plan {
+  int waves, groups;
+};
+
+static Plan decode_plan(int64_t pairs, bool tiles, int64_t steps, int D, int64_t n_max, int64_t least) {
+  const int64_t cus = device_cus(), per_cu = D == 64 && tiles ? 2 : 1;
+  int64_t w = 1, n = 1;
+  while (w < 4 && steps >= 2 * w && pairs * w * 2 <= 4 * per_cu * cus) w *= 2;
+  if (w == 4 && cus / pairs >= 3) {
+    const int64_t room = std::min<int64_t>({cus / pairs, n_max, kMaxGroups});
+    const int64_t alone = (steps + 3) / 4, each = (alone + room - 1) / room;  // steps a wave
+    const int64_t kGain = D == 64 ? 6 : 4;
+    if (alone - each >= kGain) n = (steps + 4 * each - 1) / (4 * each);
+  } else if (w == 4 && cus / pairs == 2 && n_max >= 2 && steps > 128) {
+    n = 2;
+  }
+  if (D == 64 && w == 4 && n == 1 && steps >= 24 && pairs <= cus) w = 8;
+  // More ranges asked for (up to one a step): one workgroup of eight waves if
+  // that is enough, else of four while they have a CU each (us, 1 request of 400
+  // keys, 8 kv heads: 8 ranges as 1 x 8 8.4, 2 x 4 9.1; 16 as 2 x 8 9.8, 4 x 4
+  // 7.9), else of eight, which leaves fewer partials.
+  least = std::min(least, steps);
+  if (n * w < least) {
+    if (pairs * ((least + 7) / 8) <= cus && (least <= 8 || pairs * ((least + 3) / 4) > cus)) w = 8;
+    n = std::max(n, (least + w - 1) / w);
+  }
+  return {int(w), int(n)};
 }
 
 int launch_decode_attn(const uint16_t* q, const uint16_t* k_pool, const uint16_t* v_pool, int num_blocks,
@@ -476,30 +522,13 @@ int launch_decode_attn(const uint16_t* q, const uint16_t* k_pool, const uint16_t
   const int64_t n_ct = (all_cols + 31) / 32;
   if (n_split < 1 || n_split > kMaxSplit || (n_split > 1 && n_ct > 1))
     return set_error(ILPC_EINVAL, "decode attention: bad split");
+  if (device_cus() <= 0) return set_error(ILPC_EHIP, "decode attention: cannot query the device");
   const int cols_cap = int(std::min<int64_t>(all_cols, 32));
-  // The chip holds kFill waves of this kernel (two per SIMD).  Pairs (column
-  // tiles of them) that give fewer are shared by up to eight waves of a
-  // workgroup, as far as the steps of the longest context allow: their merge
-  // inside the workgroup costs about 1 us, the second launch that merges
-  // workgroups' partials about 5.  us a decode step with its append, before ->
-  // after: 36 requests x 1000 keys, 8 kv heads 47 -> 42; 191 x 1000 (64 q
-  // heads) 147 -> 135; 100 x 2400 (4 kv heads, D 64) 67 -> 55.
   const int64_t pairs = int64_t(B) * Hkv * n_ct;
   const int64_t steps = (int64_t(max_blocks) * kBlock + kStepKeys - 1) / kStepKeys;
-  // The doubling stops where the chip is full -- at eight waves a pair a
-  // workgroup is alone on its CU, so that more than 256 would run in two
-  // rounds -- or, on long contexts, three quarters full: those run at the rate
-  // of their reads, and the finer pieces even out the CUs' shares.
-  int w = 1;
-  while (w < 8 && steps >= 2 * w &&
-         (pairs * w * 2 <= kFill || (w < 4 && steps >= 32 && pairs * w * 4 <= kFill * 3)))
-    w *= 2;
-  if (automatic) {
-    n_split = n_split > 1 && w == 8 ? auto_groups(pairs, steps, n_split) : 1;
-  } else if (n_split > 1) {
-    while (w < 8 && w < n_split) w *= 2;
-    n_split = (n_split + w - 1) / w;
-  }
+  const Plan plan = decode_plan(pairs, n_ct > 1, steps, D, n_split, automatic ? 1 : n_split);
+  const int w = plan.waves;
+  n_split = plan.groups;
   if (n_split > 1 && !part) return set_error(ILPC_EINVAL, "decode attention: no room for partial results");
   float* part_ml = part ? part + size_t(B) * Hkv * n_split * cols_cap * D : nullptr;
   const int64_t items = pairs * n_split, per_group = group_waves(w) / w;

@@ -16,16 +16,19 @@ int set_error(int code, const char* fmt, ...) __attribute__((format(printf, 2, 3
 // ilpc_paged_prefill_attn, already checked; scale_log2 = softmax scale *
 // log2(e); stream is a hipStream_t.
 // With 1 < n_split <= kMaxSplit (at most 32 columns a request) each pair's
-// keys are cut into at least n_split ranges, up to eight waves of a workgroup
-// merging theirs; past 8 the workgroups' partial states go to `part`
-// (decode_split_bytes() bytes, 16-byte aligned) and are merged by a second
-// launch.  With `automatic` n_split only bounds the workgroups a pair may take
-// (the room in `part`).
+// keys are cut into at least n_split ranges, one per wave; the waves of a
+// workgroup merge theirs, and the partial states of a pair's workgroups go to
+// `part` (decode_split_bytes() bytes, 16-byte aligned) and are merged by a
+// second launch.  With `automatic` n_split only bounds the workgroups a pair
+// may take (the room in `part`).
 int launch_decode_attn(const uint16_t* q, const uint16_t* k_pool, const uint16_t* v_pool, int num_blocks,
                        const int32_t* block_tables, int max_blocks, const int32_t* cu_q,
                        const int32_t* seq_lens, int B, int max_q_len, int Hq, int Hkv, int D,
                        float scale_log2, uint16_t* out, int n_split, bool automatic, float* part, void* stream);
 size_t decode_split_bytes(int B, int max_q_len, int Hq, int Hkv, int D, int n_split);
 constexpr int kMaxSplit = 64;
+
+// Compute units of the current device, looked up once per device (0: unknown).
+int device_cus();
 
 }  // namespace ilpc

@@ -16,18 +16,22 @@ BLOCK = 16
 
 @pytest.mark.parametrize("D,Hq,Hkv,B,L_max,rows,n_split", [
     (128, 8, 8, 300, 100, 1, 1),     # 2400 pairs: one wave each
-    (128, 32, 8, 131, 70, 1, 1),     # 1048 pairs: two waves each
-    (128, 64, 8, 33, 300, 1, 1),     # four
+    (128, 32, 8, 131, 70, 1, 1),     # 1048 pairs: one
+    (128, 64, 8, 33, 300, 1, 1),     # 264: two
+    (128, 64, 8, 64, 70, 1, 1),      # 512: two, the most pairs
+    (128, 64, 8, 32, 300, 1, 1),     # 256: four, the most pairs
     (128, 28, 4, 9, 33, 4, 1),       # 2 steps: two waves, 28 columns
     (64, 32, 2, 5, 20, 2, 1),        # 1 step, 32 columns: one wave
     (64, 12, 4, 70, 500, 1, 1),
     (128, 8, 8, 5, 200, 3, 2),       # 2 to 4 ranges: one workgroup a pair, no second launch
     (128, 32, 8, 5, 200, 1, 4),
-    (128, 32, 8, 5, 400, 2, 5),      # a second launch, uneven
-    (64, 16, 2, 3, 1000, 4, 64),
-    (128, 32, 8, 5, 400, 2, 20),     # three workgroups a pair
-    (128, 64, 8, 6, 2100, 1, 0),     # the library's choice: one workgroup a pair
-    (128, 8, 2, 2, 9000, 1, 0),      # several, and a second launch
+    (128, 32, 8, 5, 400, 2, 5),      # one workgroup of eight waves
+    (128, 64, 8, 40, 400, 2, 12),    # 320 pairs: six workgroups of two waves each
+    (64, 16, 2, 3, 1000, 4, 64),     # a range a step, in workgroups of four waves
+    (128, 32, 8, 5, 400, 2, 20),     # 13 steps: four workgroups a pair, uneven
+    (128, 32, 8, 20, 900, 1, 40),    # 160 pairs: four workgroups of eight waves
+    (128, 64, 8, 6, 2100, 1, 0),     # the library's choice: several, and a second launch
+    (128, 8, 2, 2, 9000, 1, 0),
 ])
 def test_waves_per_pair(D, Hq, Hkv, B, L_max, rows, n_split):
     def call(q, k_pool, v_pool, tables, cu, L, scale, out):
@@ -64,12 +68,18 @@ def test_few_columns_over_long_contexts(D, Hq, Hkv, B, L_max, rows):
 
 
 @pytest.mark.parametrize("D,Hq,Hkv,B,L_max,rows", [
-    (128, 64, 8, 4, 992, 1),         # 31 steps: one workgroup a pair
-    (128, 64, 8, 4, 993, 1),         # 32: four of them
-    (64, 16, 2, 1, 1300, 4),         # 41 steps in five, some ranges past the shorter rows' last key
-    (128, 28, 4, 8, 2047, 1),        # 32 pairs: the most, eight
+    (128, 64, 8, 4, 512, 1),         # 16 steps: one workgroup a pair
+    (128, 64, 8, 4, 528, 1),         # 17: five of them
+    (64, 16, 2, 4, 768, 1),          # D 64, 24 steps: one, of eight waves
+    (64, 16, 2, 4, 784, 1),          # 25: seven of four
+    (128, 64, 8, 4, 992, 1),
+    (128, 64, 8, 4, 993, 1),
+    (64, 16, 2, 1, 1300, 4),         # 41 steps in eleven, some ranges past the shorter rows' last key
+    (128, 28, 4, 8, 2047, 1),        # 32 pairs: room for eight
+    (128, 8, 2, 2, 8200, 1),         # 257 steps: sixteen, the most, uneven
     (128, 5, 5, 17, 1100, 1),        # 85 pairs: three
     (128, 4, 2, 43, 1100, 1),        # 86: one
+    (128, 4, 2, 43, 4112, 1),        # 86 pairs, 129 steps: two
 ])
 def test_library_choice_of_ranges(D, Hq, Hkv, B, L_max, rows):
     """The automatic choice, through the decode entry and, bit for bit the same, the prefill entry."""
@@ -84,6 +94,39 @@ def test_library_choice_of_ranges(D, Hq, Hkv, B, L_max, rows):
 
     _check(D, Hq, Hkv, B, L_max, rows, call)
     assert torch.equal(outs[0], outs[1])
+
+
+def test_long_contexts_take_several_compute_units():
+    """One CU takes in a pair's keys at its own rate, whatever the number of its
+    waves: ranges have to go to other CUs (measured at 8000 keys: 0.18 and 0.24 of
+    the time of one workgroup a pair; all ranges in one workgroup: 1.0)."""
+    Hq, Hkv, D, L = 32, 8, 128, 8000
+    for B, n_split, share in ((1, 0, 0.22), (2, 8, 0.5)):
+        us = []
+        for n in (1, n_split):
+            kp, vp = (torch.randn(s, device="cuda", dtype=torch.bfloat16)
+                      for s in ((B * L // BLOCK, Hkv, BLOCK, D), (B * L // BLOCK, Hkv, D, BLOCK)))
+            bt = torch.arange(B * L // BLOCK, dtype=torch.int32, device="cuda").view(B, -1)
+            cu = torch.arange(B + 1, dtype=torch.int32, device="cuda")
+            Ls = torch.full((B,), L, dtype=torch.int32, device="cuda")
+            q = torch.randn(B, Hq, D, device="cuda", dtype=torch.bfloat16)
+            out = torch.empty_like(q)
+            ws = torch.zeros(ilpc.decode_workspace_bytes(B, 1, Hq, Hkv, D, 64), dtype=torch.uint8, device="cuda")
+            stream, graph, times = torch.cuda.Stream(), torch.cuda.CUDAGraph(), []
+            torch.cuda.synchronize()
+            with torch.cuda.graph(graph, stream=stream):
+                for _ in range(50):
+                    ilpc.paged_decode_attn(q, kp, vp, bt, cu, Ls, 1, D ** -0.5, out, stream, n, ws)
+            for _ in range(7):
+                ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+                ev[0].record()
+                graph.replay()
+                ev[1].record()
+                torch.cuda.synchronize()
+                times.append(ev[0].elapsed_time(ev[1]) * 20)
+            us.append(sorted(times)[3])
+        print(f"[decode] {B} x {L} keys: one workgroup a pair {us[0]:.1f} us, n_split {n_split} {us[1]:.1f} us", flush=True)
+        assert us[1] <= share * us[0]
 
 
 def _check(D, Hq, Hkv, B, L_max, rows, call):
