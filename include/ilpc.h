@@ -251,8 +251,9 @@ int ilpc_rope_kv_append(const uint16_t* q, uint16_t* q_out, int32_t Hq, const ui
  * batches: split as for n_split = 0 when its workspace has room for
  * ilpc_decode_split() ranges, else unsplit when B * Hkv >= the device's
  * compute units; and for longer queries with few columns in the whole batch
- * (B * Hkv * ceil(max_q_len * Hq / Hkv / 32) <= 512) over contexts that may
- * reach 1024 keys (16 * max_blocks).
+ * (B * Hkv * ceil(max_q_len * Hq / Hkv / 32) at most the device's compute
+ * units, at D = 64 twice as many) over contexts that may reach 1024 keys
+ * (16 * max_blocks).
  *
  * n_split      [host] key ranges per pair, 1 .. 64, or 0 for the library's
  *                     choice.  With n > 1 a pair's keys are cut into at least

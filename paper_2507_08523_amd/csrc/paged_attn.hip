@@ -1041,19 +1041,6 @@ __global__ __launch_bounds__(kThreads, wgs_per_cu(D)) void paged_attn_kernel(
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// Compute units of the current device (one persistent workgroup each),
-// looked up once per device.
-int device_cus() {
-  static int cached[64] = {};
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0) return 0;
-  if (dev < 64 && cached[dev] > 0) return cached[dev];
-  int cus = 0;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-  if (dev < 64) cached[dev] = cus;
-  return cus;
-}
-
 int launch_status(const char* what) {
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess)
@@ -1102,7 +1089,7 @@ namespace {
 constexpr int kSplitLongSteps = 32;
 
 int decode_auto_split(int64_t B, int64_t Hkv, int64_t max_blocks) {
-  const int64_t simds = int64_t(device_cus()) * 4;
+  const int64_t simds = int64_t(ilpc::device_cus()) * 4;
   const int64_t pairs = B * Hkv;
   if (simds <= 0 || pairs <= 0 || pairs >= simds) return 1;
   int64_t n = std::min<int64_t>((simds + pairs - 1) / pairs, ilpc::kMaxSplit);
@@ -1116,16 +1103,22 @@ int decode_auto_split(int64_t B, int64_t Hkv, int64_t max_blocks) {
 
 bool decode_shaped(int64_t max_q_len, int Hq, int Hkv) { return max_q_len * (Hq / Hkv) <= kDecodeCols; }
 
-// Few query columns over long contexts: at most kFewTiles column tiles of 32
-// in the whole batch.  The persistent kernel would put them on a few CUs, each
-// running through all the keys; the decode kernel cuts the keys of a tile over
-// four or eight waves.
-constexpr int64_t kFewTiles = 512;
+// Few query columns over long contexts.  The persistent kernel would put them
+// on a few CUs, each running through all the keys; the decode kernel cuts the
+// keys of a column tile of 32 over four or eight waves.  It is the faster one
+// while its workgroups have a CU each (at D = 64 half of one).  us, decode ->
+// persistent kernel, 8 kv heads and D 128 (4 and 64), 256 tiles (512) of 8
+// requests: 1024 keys 16.9 -> 22.4 (14.0 -> 17.2), 4096 keys 43.6 -> 71.7
+// (41.6 -> 54.6), 16384 keys 184 -> 278 (149 -> 203), 200 keys in a table of
+// that width 8.6 -> 9.6; twice as many tiles, D 128: 25.6 -> 23.0, 78 -> 72, 327
+// -> 276.  A shared prefix does not move the line (the split launch over 976
+// shared keys is no faster with so few columns: 8 requests of 16 rows over 1936
+// keys, G 4, 25.4 -> 42.3).
 constexpr int64_t kFewMinKeys = 1024;  // context bound 16 * max_blocks
 
-bool few_columns(int64_t B, int64_t max_q_len, int Hq, int Hkv, int64_t max_blocks) {
+bool few_columns(int64_t B, int64_t max_q_len, int Hq, int Hkv, int D, int64_t max_blocks) {
   const int64_t tiles = B * Hkv * ((max_q_len * (Hq / Hkv) + kDecodeCols - 1) / kDecodeCols);
-  return tiles <= kFewTiles && max_blocks * kBlock >= kFewMinKeys;
+  return tiles <= int64_t(ilpc::device_cus()) * (D == 64 ? 2 : 1) && max_blocks * kBlock >= kFewMinKeys;
 }
 
 }  // namespace
@@ -1190,7 +1183,7 @@ int launch_attn(const char* fn, const uint16_t* q, const uint16_t* k_pool, const
   const int64_t items = col_tiles * Hkv * (MODE == kShared || MODE == kFused ? 1 : B);
   if (items == 0) return ILPC_OK;
   if (items >= int64_t(kAsk)) return ilpc::set_error(ILPC_EUNSUP, "%s: grid too large", fn);
-  const int cus = device_cus();
+  const int cus = ilpc::device_cus();
   if (cus <= 0) return ilpc::set_error(ILPC_EHIP, "%s: cannot query the device", fn);
   const int64_t wgs = int64_t(wgs_per_cu(D)) * cus;
   const unsigned grid = unsigned(items < wgs ? items : wgs);
@@ -1241,10 +1234,10 @@ extern "C" int ilpc_paged_prefill_attn(const uint16_t* q, const uint16_t* k_pool
       return ilpc::launch_decode_attn(q, k_pool, v_pool, num_blocks, block_tables, max_blocks, cu_q, seq_lens,
                                       B, max_q_len, Hq, Hkv, D, scale_log2, out, n_split, true,
                                       reinterpret_cast<float*>(static_cast<uint8_t*>(workspace) + head), stream);
-    if (int64_t(B) * Hkv >= device_cus())
+    if (int64_t(B) * Hkv >= ilpc::device_cus())
       return ilpc::launch_decode_attn(q, k_pool, v_pool, num_blocks, block_tables, max_blocks, cu_q, seq_lens,
                                       B, max_q_len, Hq, Hkv, D, scale_log2, out, 1, true, nullptr, stream);
-  } else if (few_columns(B, max_q_len, Hq, Hkv, max_blocks)) {
+  } else if (few_columns(B, max_q_len, Hq, Hkv, D, max_blocks)) {
     return ilpc::launch_decode_attn(q, k_pool, v_pool, num_blocks, block_tables, max_blocks, cu_q, seq_lens, B,
                                     max_q_len, Hq, Hkv, D, scale_log2, out, 1, true, nullptr, stream);
   }
@@ -1338,7 +1331,7 @@ extern "C" int ilpc_paged_prefill_attn_cascade(
   const int64_t col_tiles = (int64_t(max_q_len) * G + kCols - 1) / kCols;
   // (few_columns() as in ilpc_paged_prefill_attn, whose pass shared_len = 0 runs;
   // with so few columns the sharing saves less than the idle CUs cost)
-  if (!decode_shaped(max_q_len, Hq, Hkv) && few_columns(B, max_q_len, Hq, Hkv, max_blocks))
+  if (!decode_shaped(max_q_len, Hq, Hkv) && few_columns(B, max_q_len, Hq, Hkv, D, max_blocks))
     return ilpc::launch_decode_attn(q, k_pool, v_pool, num_blocks, block_tables, max_blocks, cu_q, seq_lens, B,
                                     max_q_len, Hq, Hkv, D, scale_log2, out, 1, true, nullptr, stream);
   if (shared_len == 0)

@@ -45,8 +45,12 @@ def test_waves_per_pair(D, Hq, Hkv, B, L_max, rows, n_split):
     (128, 28, 4, 3, 1030, 37),       # ragged group of 7, partial tiles
     (128, 8, 8, 2, 1500, 33),        # one head a group: a tile of 32 rows, then one of 1
     (64, 32, 2, 4, 1024, 61),        # the shortest context bound of this path, 248 tiles
-    (128, 32, 8, 4, 1040, 128),      # 512 tiles, the most: four waves each
-    (128, 32, 8, 4, 1040, 129),      # 544: the persistent kernel
+    (128, 32, 8, 4, 1040, 64),       # 256 tiles, the most: four waves each
+    (128, 32, 8, 4, 1040, 65),       # 288: the persistent kernel
+    (128, 32, 8, 4, 1040, 128),      # 512
+    (128, 32, 8, 4, 1040, 129),      # 544
+    (64, 32, 2, 4, 1040, 256),       # D 64: 512 tiles, the most, four waves each
+    (64, 32, 2, 4, 1040, 257),       # 520: the persistent kernel
     (64, 64, 1, 5, 1200, 3),         # 64 heads a group: two tiles a row
 ])
 def test_few_columns_over_long_contexts(D, Hq, Hkv, B, L_max, rows):
@@ -65,6 +69,28 @@ def test_few_columns_over_long_contexts(D, Hq, Hkv, B, L_max, rows):
 
     _check(D, Hq, Hkv, B, L_max, rows, call)
     assert torch.equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("D,Hq,Hkv,B,rows", [(128, 32, 8, 4, 65), (128, 32, 8, 4, 128), (64, 32, 2, 4, 257)])
+def test_the_persistent_kernel_past_the_line(D, Hq, Hkv, B, rows):
+    """More column tiles than the decode kernel has workgroups' room for go to the
+    persistent kernel: a row meets the same keys in the same order whatever the
+    batch, so that twice the batch gives the same bits."""
+    L, g = 1100, torch.Generator(device="cuda").manual_seed(rows)
+    mb, NB = -(-L // BLOCK), 2 * B * -(-L // BLOCK)
+    randn = lambda *s: torch.randn(s, generator=g, device="cuda", dtype=torch.bfloat16)  # noqa: E731
+    k_pool, v_pool, q = randn(NB, Hkv, BLOCK, D), randn(NB, Hkv, D, BLOCK), randn(2 * B * rows, Hq, D)
+    tables = torch.randperm(NB, generator=g, device="cuda").to(torch.int32).view(2 * B, mb)
+    outs = []
+    for n in (B, 2 * B):
+        cu = torch.arange(n + 1, dtype=torch.int32, device="cuda") * rows
+        Ls = torch.full((n,), L, dtype=torch.int32, device="cuda")
+        out = torch.full_like(q[:n * rows], float("nan"))
+        ws = torch.zeros(64, dtype=torch.uint8, device="cuda")
+        ilpc.paged_prefill_attn(q[:n * rows], k_pool, v_pool, tables[:n], cu, Ls, rows, D ** -0.5, out, ws)
+        outs.append(out)
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0], outs[1][:B * rows])
 
 
 @pytest.mark.parametrize("D,Hq,Hkv,B,L_max,rows", [
