@@ -248,9 +248,8 @@ int ilpc_rope_kv_append(const uint16_t* q, uint16_t* q_out, int32_t Hq, const ui
  * pools;
  * results agree with ilpc_paged_prefill_attn to the attention tolerance, not
  * bit for bit.  ilpc_paged_prefill_attn takes this path by itself for such
- * batches: split as for n_split = 0 when its workspace has room for
- * ilpc_decode_split() ranges, else unsplit when B * Hkv >= the device's
- * compute units; and for longer queries with few columns in the whole batch
+ * batches, as for n_split = 0 but with no more workgroups a pair than its
+ * workspace has room for partial results; and for longer queries with few columns in the whole batch
  * (B * Hkv * ceil(max_q_len * Hq / Hkv / 32) at most the device's compute
  * units, at D = 64 twice as many) over contexts that may reach 1024 keys
  * (16 * max_blocks).
@@ -276,12 +275,10 @@ int ilpc_paged_decode_attn(const uint16_t* q, const uint16_t* k_pool, const uint
                            uint16_t* out, int32_t n_split, void* workspace, size_t workspace_bytes,
                            void* stream);
 
-/* The most key ranges with partial results in the workspace that
- * ilpc_paged_decode_attn takes for n_split = 0 on the current device: 1 when
- * B * Hkv >= its SIMDs (4 per compute unit), and when B * Hkv >= half of them
- * with a context bound 16 * max_blocks under 1024 tokens; otherwise enough
- * ranges for one wave per SIMD, at most one per 32 keys of that bound, at most
- * 64. */
+/* The most workgroups a pair, and so the most partial results in the
+ * workspace, that ilpc_paged_decode_attn takes for n_split = 0 on the current
+ * device: the compute units / (B * Hkv), at most one per 128 keys of the bound
+ * 16 * max_blocks, at most 16, at least 1. */
 int ilpc_decode_split(int32_t B, int32_t Hkv, int32_t max_blocks, int32_t* n_split);
 
 /* Workspace bytes of ilpc_paged_decode_attn with n_split ranges:
@@ -291,11 +288,12 @@ int ilpc_decode_workspace_bytes(int32_t B, int32_t max_q_len, int32_t Hq, int32_
 
 /* Bytes of device workspace ilpc_paged_prefill_attn needs for these sizes:
  * 64 (the counters of its work queues), plus, for decode-shaped batches
- * (max_q_len * Hq / Hkv <= 32) with fewer (request, kv head) pairs than the
- * current device has SIMDs, room for the split decode kernel's partials
- * (ilpc_decode_workspace_bytes() at the split of any context length).  A
- * workspace of only 64 bytes is still accepted: such batches then run
- * unsplit. */
+ * (max_q_len * Hq / Hkv <= 32), room for the decode kernel's partial results
+ * on every batch of at most B such requests:
+ * min(16 * B * Hkv, the current device's compute units) *
+ * (max_q_len * Hq / Hkv) * (D + 2) * 4.  A smaller workspace, down to 64
+ * bytes, is still accepted: such batches then run with fewer workgroups a
+ * pair. */
 int ilpc_attn_workspace_bytes(int32_t B, int32_t max_q_len, int32_t Hq, int32_t Hkv, int32_t D,
                               size_t* bytes);
 
@@ -349,9 +347,9 @@ int ilpc_paged_prefill_attn(const uint16_t* q, const uint16_t* k_pool, const uin
  * ilpc_paged_prefill_attn with a workspace of 8 MiB + 256 bytes, and the
  * kernels are the same: the first 64 bytes hold the work-queue counters
  * (zero when the library is loaded; every call leaves them zero again), and
- * decode-shaped batches split their keys over several waves only when the
- * split's partial results fit in the rest (else they run unsplit), so no
- * batch needs more scratch than the array holds and none is refused for its
+ * the rest takes the partial results of decode-shaped batches, all that
+ * ilpc_attn_workspace_bytes() asks for on devices of up to 512 compute units
+ * (fewer workgroups run if they do not fit), so no batch is refused for its
  * size.  Every call on a GPU shares that GPU's array: calls that may overlap
  * on one GPU (different streams, other threads) race and must not be issued;
  * calls ordered on one stream are safe.  ILPC_EHIP if the array's address

@@ -512,6 +512,18 @@ static Plan decode_plan(int64_t pairs, bool tiles, int64_t steps, int D, int64_t
   return {int(w), int(n)};
 }
 
+int decode_max_groups(int64_t pairs, int64_t steps) {
+  if (pairs <= 0) return 1;
+  const int64_t n = std::min<int64_t>(device_cus() / pairs, kMaxGroups);
+  return int(std::max<int64_t>(1, steps > 0 ? std::min(n, (steps + 3) / 4) : n));
+}
+
+size_t decode_auto_bytes(int64_t pairs, int max_q_len, int Hq, int Hkv, int D) {
+  const int64_t sets = std::min<int64_t>(pairs * kMaxGroups, device_cus());
+  const int64_t cols = std::min<int64_t>(int64_t(max_q_len) * (Hq / Hkv), 32);
+  return size_t(sets) * cols * (D + 2) * sizeof(float);
+}
+
 int launch_decode_attn(const uint16_t* q, const uint16_t* k_pool, const uint16_t* v_pool, int num_blocks,
                        const int32_t* block_tables, int max_blocks, const int32_t* cu_q,
                        const int32_t* seq_lens, int B, int max_q_len, int Hq, int Hkv, int D,

@@ -28,6 +28,12 @@ int launch_decode_attn(const uint16_t* q, const uint16_t* k_pool, const uint16_t
 size_t decode_split_bytes(int B, int max_q_len, int Hq, int Hkv, int D, int n_split);
 constexpr int kMaxSplit = 64;
 
+// The most workgroups to a (request, kv head) pair an automatic launch takes
+// (steps: 32-key steps of the longest context; 0: any), and the bytes of
+// partial states with which no batch of at most `pairs` pairs takes fewer.
+int decode_max_groups(int64_t pairs, int64_t steps);
+size_t decode_auto_bytes(int64_t pairs, int max_q_len, int Hq, int Hkv, int D);
+
 // Compute units of the current device, looked up once per device (0: unknown).
 int device_cus();
 

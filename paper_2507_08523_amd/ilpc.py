@@ -460,7 +460,7 @@ def paged_prefill_attn(q, k_pool, v_pool, block_tables, cu_q, seq_lens, max_q_le
     `workspace` defaults to the buffer attn_workspace() keeps for the stream
     the call is issued on, grown to attn_workspace_bytes() for this shape
     (decode-shaped batches with few (request, kv head) pairs use the room to
-    split each pair's keys over several waves).
+    cut each pair's keys over several workgroups).
     """
     import torch
 
@@ -518,7 +518,7 @@ NOALLOC_SCRATCH_BYTES = 256 + (8 << 20)
 
 
 def decode_split(B, Hkv, max_blocks) -> int:
-    """Key ranges per (request, kv head) the decode kernel uses by default."""
+    """The most workgroups per (request, kv head) pair the decode kernel takes with n_split = 0."""
     n = _i32()
     _check(load().ilpc_decode_split(B, Hkv, max_blocks, ctypes.byref(n)))
     return int(n.value)
@@ -533,13 +533,12 @@ def decode_workspace_bytes(B, max_q_len, Hq, Hkv, D, n_split) -> int:
 def paged_decode_attn(q, k_pool, v_pool, block_tables, cu_q, seq_lens, max_q_len: int, scale: float, out,
                       stream=None, n_split: int = 1, workspace=None):
     """The decode kernel alone (max_q_len * Hq / Hkv <= 32): same semantics as
-    paged_prefill_attn, which picks it by itself (unsplit) for such batches
-    when they have at least one (request, kv head) pair per compute unit.
+    paged_prefill_attn, which picks it by itself for such batches.
 
-    n_split > 1 cuts every pair's keys into that many ranges (0: the
-    library's choice, decode_split()); `workspace` is then a uint8 device
-    tensor of at least decode_workspace_bytes() bytes, allocated here when
-    omitted (an allocation: pass one in under graph capture).
+    n_split > 1 cuts every pair's keys into at least that many ranges, one per
+    wave (0: the library's choice); `workspace` is then a uint8 device tensor
+    of at least decode_workspace_bytes() bytes at n_split (0: decode_split()),
+    allocated here when omitted (an allocation: pass one in under graph capture).
     """
     import torch
 

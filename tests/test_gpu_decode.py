@@ -104,8 +104,7 @@ def test_decode_kernel_against_oracle(name, n_prompts, q_len):
                            sp.scale, out)
     torch.cuda.synchronize()
     f.check(out, cu, qn, f"q_len {q_len}")
-    # the same batch through the prefill entry (fewer pairs than compute units:
-    # the persistent kernel)
+    # the same batch through the prefill entry (the library's choice of workgroups)
     out2 = torch.empty_like(q)
     f.pc.attend(b, q, out2, sp.scale)
     torch.cuda.synchronize()
@@ -133,8 +132,7 @@ def test_decode_kernel_short_contexts_and_rejection():
 
 def test_prefill_entry_takes_the_decode_kernel_for_wide_batches():
     # 64 prompts x 8 kv heads = 512 pairs >= 256 compute units: the automatic
-    # path is the decode kernel, split as the library chooses when the
-    # workspace has room (fewer pairs than SIMDs), unsplit with 64 bytes
+    # path is the decode kernel, one workgroup a pair with and without room for more
     f = Full(workload.scaled_spec("large", 64))
     sp = f.wl.spec
     q, cu, qn = f.queries(1)
@@ -157,7 +155,7 @@ def test_prefill_entry_takes_the_decode_kernel_for_wide_batches():
 def test_prefill_entry_splits_small_decode_batches():
     # 6 prompts x 8 kv heads = 48 pairs: with a full-size workspace the entry
     # runs the split decode kernel (the same bits as the library's split
-    # choice); with only the 64 queue bytes, the persistent kernel
+    # choice); with only the 64 queue bytes, one workgroup a pair
     f = Full(workload.scaled_spec("large", 6))
     sp = f.wl.spec
     q, cu, qn = f.queries(1)
@@ -179,5 +177,5 @@ def test_prefill_entry_splits_small_decode_batches():
     torch.cuda.synchronize()
     assert torch.equal(out_entry, out_split)
     assert int(ws[:64].count_nonzero()) == 0 and int(small.count_nonzero()) == 0
-    f.check(out_entry, cu, qn, f"prefill entry, {n} key ranges")
+    f.check(out_entry, cu, qn, f"prefill entry, up to {n} workgroups a pair")
     f.check(out_small, cu, qn, "prefill entry, 64-byte workspace")

@@ -122,6 +122,51 @@ def test_library_choice_of_ranges(D, Hq, Hkv, B, L_max, rows):
     assert torch.equal(outs[0], outs[1])
 
 
+@pytest.mark.parametrize("B,L_max,rows,room,n_split", [
+    (4, 2100, 1, 0, 1),          # 64 bytes: one workgroup a pair, and no workspace needed
+    (1, 90, 3, 0, 1),
+    (4, 2100, 1, 3, 3),          # room for three workgroups a pair
+    (4, 2100, 1, 7, 7),
+    (2, 1100, 8, 64, 0),         # all that the library asks for
+])
+def test_decode_shapes_in_small_workspaces(B, L_max, rows, room, n_split):
+    """The prefill entry takes the decode kernel with as many workgroups a pair as
+    the workspace has room for: the bits of the decode entry."""
+    D, Hq, Hkv = 128, 32, 8
+    outs = []
+
+    def call(q, k_pool, v_pool, tables, cu, L, scale, out):
+        ilpc.paged_decode_attn(q, k_pool, v_pool, tables, cu, L, rows, scale, out, n_split=n_split)
+        need = ilpc.decode_workspace_bytes(B, rows, Hq, Hkv, D, room) if room > 1 else 0
+        ws = torch.zeros(64 + need, dtype=torch.uint8, device="cuda")
+        other = torch.full_like(out, float("nan"))
+        ilpc.paged_prefill_attn(q, k_pool, v_pool, tables, cu, L, rows, scale, other, ws)
+        outs.extend([out, other])
+
+    _check(D, Hq, Hkv, B, L_max, rows, call)
+    assert torch.equal(outs[0], outs[1])
+
+
+def test_static_scratch_holds_every_automatic_split():
+    """32 columns over long contexts: the static scratch has room for the same split
+    as a workspace of the size asked for, and a workspace for the largest batch for
+    every smaller one."""
+    B, Hq, Hkv, D, rows = 4, 32, 8, 128, 8
+    outs = []
+
+    def call(q, k_pool, v_pool, tables, cu, L, scale, out):
+        ilpc.paged_prefill_attn_noalloc(q, k_pool, v_pool, tables, cu, L, rows, scale, out)
+        ilpc.paged_decode_attn(q, k_pool, v_pool, tables, cu, L, rows, scale, other := torch.empty_like(out), n_split=0)
+        outs.extend([out, other])
+
+    _check(D, Hq, Hkv, B, 2500, rows, call)
+    assert torch.equal(outs[0], outs[1])
+    need = [ilpc.attn_workspace_bytes(b, rows, Hq, Hkv, D) for b in range(1, 200)]
+    assert need == sorted(need) and need[-1] <= ilpc.NOALLOC_SCRATCH_BYTES
+    for b, n in enumerate(need, 1):
+        assert n >= 64 + ilpc.decode_workspace_bytes(b, rows, Hq, Hkv, D, ilpc.decode_split(b, Hkv, 1 << 20))
+
+
 def test_long_contexts_take_several_compute_units():
     """One CU takes in a pair's keys at its own rate, whatever the number of its
     waves: ranges have to go to other CUs (measured at 8000 keys: 0.18 and 0.24 of
