@@ -229,6 +229,7 @@ constexpr int kQueueWords = 16;  // workspace: 8 queue counters, finished workgr
 constexpr int kDoneWord = 8;
 constexpr int kDrainedWord = 9;
 constexpr unsigned kLongRounds = 16;
+constexpr int kIndex = 2048;  // COUNTED: groups of requests, and one
 constexpr unsigned kNoItem = ~0u, kAsk = ~0u - 1u;
 
 // s_waitcnt vmcnt(n) with the other counters left free (n < 16).
@@ -280,14 +281,14 @@ constexpr int kFusedReqs = kCols + 4;
 // D = 64 three.
 constexpr int wgs_per_cu(int D) { return D == 64 ? 3 : 2; }
 
-template <int D, int MODE>
+template <int D, int MODE, bool COUNTED>
 __global__ __launch_bounds__(kThreads, wgs_per_cu(D)) void paged_attn_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_pool,
     const uint16_t* __restrict__ v_pool, int num_blocks, const int32_t* __restrict__ block_tables,
     int max_blocks, const int32_t* __restrict__ cu_q, const int32_t* __restrict__ seq_lens, int n_req,
-    int Hq, int Hkv, int n_col_tiles, unsigned n_items, unsigned chunk, float scale_log2, uint16_t* __restrict__ out,
-    unsigned* __restrict__ queue, int kv_split, float* __restrict__ part_o, float* __restrict__ part_ml,
-    int part_rows) {
+    int Hq, int Hkv, int n_col_tiles, unsigned n_items, unsigned chunk, int count_shift, float scale_log2,
+    uint16_t* __restrict__ out, unsigned* __restrict__ queue, int kv_split, float* __restrict__ part_o,
+    float* __restrict__ part_ml, int part_rows) {
   constexpr int kDch = D / 16;                    // 16-wide contraction chunks of Q.K^T
   constexpr int kDt = D / 32;                     // 32-row output tiles of O^T
   constexpr int kRowBytes = D * 2;                // one K row in LDS
@@ -306,12 +307,74 @@ __global__ __launch_bounds__(kThreads, wgs_per_cu(D)) void paged_attn_kernel(
   __shared__ uint32_t f_tile[kIsFused ? kFusedTiles : 1];
   __shared__ int f_req[kIsFused ? kFusedReqs : 1], f_lim[kIsFused ? kFusedReqs : 1];
   __shared__ int f_count;
+  constexpr bool kWholeBatch = MODE == kShared || MODE == kFused;  // items are columns of the whole batch
+  // COUNTED: column tiles (of one kv head) before each group of 2^count_shift
+  // requests, and behind the last one.
+  static_assert(!(COUNTED && kWholeBatch), "those modes know their rows");
+  __shared__ unsigned first_tile[COUNTED ? kIndex : 1];
+  __shared__ unsigned s_sums[COUNTED ? kWaves : 1];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform
   const int n = lane & 31, hh = lane >> 5;
   const int G = Hq / Hkv;
   const size_t slab_stride = size_t(Hkv) * kSlabBytes;
+
+  // The host sizes a launch by max_q_len.  With many numbers (count_shift >= 0)
+  // the kernel first counts the column tiles there are, and numbers only those:
+  // a batch with one long request among many short ones is nearly all empty
+  // numbers otherwise, each of them an atomic on the shared counters.  us, one
+  // by one (in the 8-wave layout, half as many) -> counted, 32/8 heads: 64
+  // requests of 1 row but one of 4000 890 (546) -> 188, 256 and one of 2000 1537
+  // (795) -> 102, 128 of 16 and one of 1000 445 (237) -> 59; where all hold work
+  // the count costs 1 to 2 us (128 prompts of 1024 rows 1290 -> 1301).
+  int n_groups = 0;
+  auto tiles_of = [&](int r) -> unsigned {  // column tiles of request r
+    int a = cu_q[r], b = cu_q[r + 1];
+    if constexpr (MODE == kSuffix) b = min(b, part_rows);
+    return b <= a ? 0u : unsigned(min((int64_t(b - a) * G + (kCols - 1)) / kCols, int64_t(n_col_tiles)));
+  };
+  if constexpr (COUNTED) {
+    // every thread a run of groups; then a sum over the threads before it
+    n_groups = (n_req + (1 << count_shift) - 1) >> count_shift;
+    const int per = (n_groups + kThreads - 1) / kThreads;
+    const int g0 = min(tid * per, n_groups), g1 = min(g0 + per, n_groups);
+    unsigned mine = 0;
+    for (int g = g0; g < g1; ++g) {
+      unsigned t = 0;
+      for (int r = g << count_shift; r < min((g + 1) << count_shift, n_req); ++r) t += tiles_of(r);
+      first_tile[g] = t;
+      mine += t;
+    }
+    unsigned sum = mine;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const unsigned v = __shfl_up(sum, off);
+      sum += lane >= off ? v : 0u;
+    }
+    if (lane == 63) s_sums[wave] = sum;
+    __syncthreads();
+    unsigned before = sum - mine;
+    for (int i = 0; i < wave; ++i) before += s_sums[i];
+    for (int g = g0; g < g1; ++g) {
+      const unsigned t = first_tile[g];
+      first_tile[g] = before;
+      before += t;
+    }
+    if (tid == kThreads - 1) first_tile[n_groups] = before;
+    __syncthreads();
+    n_items = __builtin_amdgcn_readfirstlane(first_tile[n_groups]) * unsigned(Hkv);
+  } else if (kWholeBatch && count_shift >= 0) {
+    int rows = scalar_load(cu_q + n_req);
+    if constexpr (MODE == kShared) rows = min(rows, part_rows);
+    n_col_tiles = int(min((int64_t(max(rows, 0)) * G + (kCols - 1)) / kCols, int64_t(n_col_tiles)));
+    n_items = unsigned(n_col_tiles) * unsigned(Hkv);
+  }
+  if ((COUNTED || kWholeBatch) && count_shift >= 0) {
+    if (n_items == 0) return;
+    // (odd: a run of equal pairs must not put the same part of each into one queue)
+    chunk = n_items >= kLongRounds * gridDim.x ? (n_items + 7u) / 8u : max(n_items / 256u, 1u) | 1u;
+  }
 
   // Hand-out of the items.  Item numbers are cut into chunks of `chunk`; queue
   // x (one per XCD) holds the chunks x, x + 8, ..., and is worked by the
@@ -462,10 +525,41 @@ __global__ __launch_bounds__(kThreads, wgs_per_cu(D)) void paged_attn_kernel(
     w = __builtin_amdgcn_readfirstlane(w);
     // kFused numbers items kv-head-major (the items of one kv head share the
     // prefix blocks, under one XCD's L2).
-    const int tile = kIsFused ? int(w % unsigned(n_col_tiles)) : n_col_tiles - 1 - int(w % unsigned(n_col_tiles));
-    const unsigned rest = w / unsigned(n_col_tiles);
-    kvh = kIsFused ? int(rest) : int(rest % unsigned(Hkv));
-    const int r = MODE == kShared || kIsFused ? 0 : int(rest / unsigned(Hkv));
+    int tile, r = 0;
+    if constexpr (COUNTED) {
+      // The last group that starts at or before tile w / Hkv: every 32nd first,
+      // then the 32 behind it.
+      const unsigned at = w / unsigned(Hkv);
+      constexpr int kStride = kIndex / 64;
+      const int blk = __popcll(__ballot(first_tile[min(lane * kStride, n_groups)] <= at)) - 1;
+      const bool here = lane < kStride && first_tile[min(blk * kStride + lane, n_groups)] <= at;
+      const int g = blk * kStride + __popcll(__ballot(here)) - 1;
+      r = g << count_shift;
+      unsigned base = __builtin_amdgcn_readfirstlane(first_tile[g]);
+      unsigned tiles = __builtin_amdgcn_readfirstlane(first_tile[g + 1]) - base;
+      if (count_shift > 0) {  // which of the group's requests (at most 64)
+        const bool in = lane < (1 << count_shift) && r + lane < n_req;
+        const unsigned t = in ? tiles_of(r + lane) : 0u;
+        unsigned sum = t;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+          const unsigned v = __shfl_up(sum, off);
+          sum += lane >= off ? v : 0u;
+        }
+        const int l = __popcll(__ballot(base + sum <= at));  // requests that end at or before it
+        tiles = __builtin_amdgcn_readlane(t, l);
+        base += __builtin_amdgcn_readlane(sum, l) - tiles;
+        r += l;
+      }
+      const unsigned in_r = w - base * unsigned(Hkv);
+      kvh = int(in_r / tiles);
+      tile = int(tiles - 1u - in_r % tiles);
+    } else {
+      tile = kIsFused ? int(w % unsigned(n_col_tiles)) : n_col_tiles - 1 - int(w % unsigned(n_col_tiles));
+      const unsigned rest = w / unsigned(n_col_tiles);
+      kvh = kIsFused ? int(rest) : int(rest % unsigned(Hkv));
+      if (!kWholeBatch) r = int(rest / unsigned(Hkv));
+    }
     // First key tile of this launch (the suffix half starts at kv_split).
     t0 = MODE == kSuffix ? kv_split / kKeys : 0;
     // This item's lengths and the block ids of its first three tiles are
@@ -1174,18 +1268,36 @@ int launch_attn(const char* fn, const uint16_t* q, const uint16_t* k_pool, const
   // (request, kv head) pairs, whose items read the same K/V, when they deal out
   // evenly (or nearly so), else pieces that do.
   const int64_t pairs = items / col_tiles;
+  // Whether the kernel counts the numbers that hold work: where there are many,
+  // more than one to a pair (kWholeBatch: to a kv head); and from half as many
+  // on where one request could hold most of the work and would put it on fewer
+  // than eight queues, several rounds of it.  Below, taking the empty ones by
+  // position costs less than the count does on a batch without any (8 rounds
+  // of 64 rows over 200 keys 125 -> 128 us).
+  const bool counted =
+      col_tiles > 1 && B <= (kIndex - 1) * 64 &&
+      (items >= int64_t(kLongRounds) * grid ||
+       (MODE == kFull && Hkv < 8 && col_tiles * 16 >= 5 * int64_t(grid) && items >= int64_t(kLongRounds / 2) * grid));
+  int shift = 0;
+  while (((B - 1) >> shift) + 1 > kIndex - 1) ++shift;
   const unsigned chunk = unsigned(
       items >= int64_t(kLongRounds) * grid ? (items + 7) / 8
       : pairs % 8 == 0 || pairs >= 256     ? col_tiles
                                            : std::max<int64_t>(items / 256, 1));
-  if (D == 128)
-    hipLaunchKernelGGL((paged_attn_kernel<128, MODE>), dim3(grid), dim3(kThreads), 0, s, q, k_pool, v_pool,
-                       num_blocks, block_tables, max_blocks, cu_q, seq_lens, B, Hq, Hkv, int(col_tiles),
-                       unsigned(items), chunk, scale_log2, out, queue, kv_split, part_o, part_ml, part_rows);
-  else
-    hipLaunchKernelGGL((paged_attn_kernel<64, MODE>), dim3(grid), dim3(kThreads), 0, s, q, k_pool, v_pool,
-                       num_blocks, block_tables, max_blocks, cu_q, seq_lens, B, Hq, Hkv, int(col_tiles),
-                       unsigned(items), chunk, scale_log2, out, queue, kv_split, part_o, part_ml, part_rows);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), 0, s, q, k_pool, v_pool, num_blocks, block_tables, max_blocks,
+                       cu_q, seq_lens, B, Hq, Hkv, int(col_tiles), unsigned(items), chunk, counted ? shift : -1,
+                       scale_log2, out, queue, kv_split, part_o, part_ml, part_rows);
+  };
+  if constexpr (MODE == kFull || MODE == kSuffix) {
+    if (counted) {
+      if (D == 128) launch(paged_attn_kernel<128, MODE, true>);
+      else launch(paged_attn_kernel<64, MODE, true>);
+      return launch_status(fn);
+    }
+  }
+  if (D == 128) launch(paged_attn_kernel<128, MODE, false>);
+  else launch(paged_attn_kernel<64, MODE, false>);
   return launch_status(fn);
 }
 
