@@ -3,7 +3,8 @@
 
 Argument marshalling only: every step of the path runs in the library (host
 C++ prefix matching, HIP kernels for K/V append and attention).  Loading fails
-loudly if the library has not been built; there is no fallback.
+loudly if the library has not been built; there is no fallback.  The native
+calls are only a faster way into it.
 
 Device tensors are torch tensors (PyTorch supplies device memory and streams);
 they are checked for dtype, device, contiguity and shape before their
@@ -13,6 +14,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 
 import numpy as np
 
@@ -97,14 +99,16 @@ def load():
 
 
 class _NoNative:
-    """Stands in for the native binding where torch knows no GPU: takes no call."""
+    """Stands in for the native binding where there is none: takes no call."""
 
     def __getattr__(self, name):
         return lambda *args: None
 
 
 def _native():
-    """The native part of the binding, bound to the loaded library; raises if it has not been built."""
+    """The native part of the binding, bound to the loaded library.  Where it cannot be loaded (not
+    built, or built against another torch) every call goes through ctypes, with a warning once: the
+    same kernels, about 14 us of host time a call more."""
     global _binding
     if _binding is None:
         import torch
@@ -116,8 +120,10 @@ def _native():
         try:
             from . import _binding as mod
         except ImportError as e:
-            raise ILPCError(EINVAL, f"the native binding cannot be loaded ({e}): run "
-                                    f"`python -m paper_2507_08523_amd.build`") from e
+            warnings.warn(f"the native binding cannot be loaded ({e}), device calls go through ctypes: run "
+                          f"`python -m paper_2507_08523_amd.build`", RuntimeWarning, stacklevel=3)
+            _binding = _NoNative()
+            return _binding
         mod.bind(*(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in (
             "ilpc_kv_append", "ilpc_rope_kv_append", "ilpc_attn_workspace_bytes", "ilpc_paged_prefill_attn",
             "ilpc_paged_prefill_attn_cascade")))

@@ -1,5 +1,7 @@
 """The native device calls of the binding against its general path: the same
 bytes for every form that they take, and the same error for what is refused."""
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -129,6 +131,38 @@ def refusals(device, monkeypatch):
 def test_refusals_on_the_cpu_equal_the_general_path(monkeypatch):
     said = refusals("cpu", monkeypatch)
     assert all(s[2] is not None for s in said)  # (no tensor is on a GPU)
+
+
+def test_without_the_native_binding_calls_go_through_ctypes(monkeypatch):
+    # not built, or built against another torch: a warning, and the general path's answer
+    monkeypatch.setattr(ilpc, "_binding", None)
+    monkeypatch.setitem(sys.modules, "paper_2507_08523_amd._binding", None)  # (importing it raises ImportError)
+    monkeypatch.delattr("paper_2507_08523_amd._binding", raising=False)
+    monkeypatch.setattr(torch.version, "hip", "7")
+    with pytest.warns(RuntimeWarning, match="native binding"):
+        with pytest.raises(ilpc.ILPCError, match="must be a CUDA/HIP torch tensor"):
+            append(make("cpu"))
+    assert isinstance(ilpc._binding, ilpc._NoNative)
+
+
+def test_build_without_a_host_compiler_keeps_the_library(monkeypatch, tmp_path, capsys):
+    from paper_2507_08523_amd import build
+
+    stale = tmp_path / "_binding.so"
+    stale.write_bytes(b"old")
+    monkeypatch.setattr(build, "LIB", str(tmp_path / "libilpc.so"))
+    monkeypatch.setattr(build, "BINDING", str(stale))
+
+    def run(cmd, **kw):
+        if cmd[0] == "g++":
+            raise FileNotFoundError("g++")
+        (tmp_path / "libilpc.so.tmp").write_bytes(b"lib")
+        return build.subprocess.CompletedProcess(cmd, 0, "", "")
+
+    monkeypatch.setattr(build.subprocess, "run", run)
+    monkeypatch.setattr(torch.version, "hip", "7")
+    assert build.build() == str(tmp_path / "libilpc.so")
+    assert not stale.exists() and "no native binding" in capsys.readouterr().err
 
 
 @pytest.mark.gpu
