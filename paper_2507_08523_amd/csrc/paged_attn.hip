@@ -27,15 +27,18 @@
 //      accumulator layout of S^T equal the operand layout P^T needs).
 //    What bounds it: on large batches the power limit (zeros for inputs run
 //    25-30% faster, at the same instructions), on small ones the latency of an
-//    item's start and the number of items in flight.  One 8-wave workgroup per
-//    CU on 256-column items, its halves a phase apart, was the layout before:
-//    the same time on large batches, but half as many items and workgroups to
-//    fill the chip with, all waves stopping at every item boundary, and its
-//    items fetched one by one from contended counters.  Attention launch,
-//    before -> now: 20 scheduler steps of 1024 tokens (32/8 heads, 604 keys)
+//    item's start and the number of items in flight.  Large batches at head size
+//    128 take a wide layout: one 8-wave workgroup per CU on 256-column items, its
+//    halves a phase apart, which loads every K/V tile into LDS half as often.
+//    For all others it has half as many items and workgroups to fill the chip
+//    with.  Attention launch, an 8-wave layout of two barriers a tile, with its
+//    items fetched one by one from contended counters, -> now: 20 scheduler steps of 1024 tokens (32/8 heads, 604 keys)
 //    538 -> 474 us with their appends; 64 prompts of 300 new tokens, half
 //    cached 210 -> 180 us; 128 prompts of 48 new tokens after 976 shared ones
 //    120 -> 107 us; 199 prompts of 118 tokens (16/2 heads, D 64) 76 -> 40 us.
+//    The wide layout, that one -> narrow -> now, us: 512 prompts of 64 new tokens
+//    after 2048 own ones (64/8 heads) 2272 -> 2297 -> 2252; 128 of 1024 (32/8)
+//    1296 -> 1309 -> 1245; 128 of 1984 after 128 (64/8) 8621 -> 8621 -> 8363.
 //  * the same attention split at a prefix every request of the batch shares
 //    (modes kShared / kSuffix: two launches; kFused: one launch whose items
 //    are 128 columns of the whole batch, over the shared tiles and then each
@@ -60,8 +63,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBlock = 16;                    // tokens per pool block
-constexpr int kWaves = 4;                     // waves per attention workgroup (two workgroups per CU)
-constexpr int kThreads = 64 * kWaves;
+constexpr int kWaves = 4;                     // waves per attention workgroup (two workgroups per CU); wide: 8 (one)
 constexpr int kColsPerWave = 32;              // query columns per wave (MFMA N)
 constexpr int kCols = kColsPerWave * kWaves;  // query columns per workgroup
 constexpr int kKeys = 64;                     // keys per tile
@@ -229,6 +231,7 @@ constexpr int kQueueWords = 16;  // workspace: 8 queue counters, finished workgr
 constexpr int kDoneWord = 8;
 constexpr int kDrainedWord = 9;
 constexpr unsigned kLongRounds = 16;
+constexpr int kWideRounds = 8;  // items of the wide layout to a CU from which it runs
 constexpr int kIndex = 2048;  // COUNTED: groups of requests, and one
 constexpr unsigned kNoItem = ~0u, kAsk = ~0u - 1u;
 
@@ -281,8 +284,8 @@ constexpr int kFusedReqs = kCols + 4;
 // D = 64 three.
 constexpr int wgs_per_cu(int D) { return D == 64 ? 3 : 2; }
 
-template <int D, int MODE, bool COUNTED>
-__global__ __launch_bounds__(kThreads, wgs_per_cu(D)) void paged_attn_kernel(
+template <int D, int MODE, bool COUNTED, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, wgs_per_cu(D)) void paged_attn_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_pool,
     const uint16_t* __restrict__ v_pool, int num_blocks, const int32_t* __restrict__ block_tables,
     int max_blocks, const int32_t* __restrict__ cu_q, const int32_t* __restrict__ seq_lens, int n_req,
@@ -296,9 +299,12 @@ __global__ __launch_bounds__(kThreads, wgs_per_cu(D)) void paged_attn_kernel(
   constexpr int kSlabBytes = kBlock * D * 2;      // one (block, kv head) slab: in a pool, and in LDS
   constexpr int kTileBytes = kTileBlocks * kSlabBytes;  // one K tile, or one V tile
   constexpr int kInsts = kSlabBytes / 1024;       // 1 KB direct loads of a slab
-  static_assert(kWaves == kTileBlocks, "each wave loads one pool block of a tile");
-  // Two K tiles, then two V tiles.
-  __shared__ __attribute__((aligned(16))) uint8_t ring[4 * kTileBytes];
+  constexpr int kThreads = 64 * WAVES, kCols = kColsPerWave * WAVES;
+  constexpr bool kWide = WAVES == 2 * kTileBlocks;
+  static_assert(kWide || WAVES == kTileBlocks, "a wave loads the K and the V of a pool block, or (kWide) one of them");
+  // K tiles, then as many V tiles.
+  constexpr int kBufs = kWide ? 3 : 2;
+  __shared__ __attribute__((aligned(16))) uint8_t ring[2 * kBufs * kTileBytes];
   __shared__ unsigned s_item;
   // kFused: tile T_s + i of an item is tile f_tile[i] & 0xFFFFFF of the item's
   // request number f_tile[i] >> 24, which is request f_req[.], whose keys at
@@ -312,14 +318,21 @@ __global__ __launch_bounds__(kThreads, wgs_per_cu(D)) void paged_attn_kernel(
   // requests, and behind the last one.
   static_assert(!(COUNTED && kWholeBatch), "those modes know their rows");
   __shared__ unsigned first_tile[COUNTED ? kIndex : 1];
-  __shared__ unsigned s_sums[COUNTED ? kWaves : 1];
+  __shared__ unsigned s_sums[COUNTED ? WAVES : 1];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform
   const int n = lane & 31, hh = lane >> 5;
+  const int blk = kWide ? wave & (kTileBlocks - 1) : wave;  // pool block of a tile this wave loads
+  const bool lag = kWide && wave >= kTileBlocks;            // (kWide) the half that runs a phase behind, and loads V
   const int G = Hq / Hkv;
   const size_t slab_stride = size_t(Hkv) * kSlabBytes;
 
+  // Two layouts, one of which runs: the wide one from part_rows rows on (kFull;
+  // 0: only one is launched).
+  if constexpr (MODE == kFull && COUNTED) {
+    if (part_rows > 0 && (scalar_load(cu_q + n_req) >= part_rows) != kWide) return;
+  }
   // The host sizes a launch by max_q_len.  With many numbers (count_shift >= 0)
   // the kernel first counts the column tiles there are, and numbers only those:
   // a batch with one long request among many short ones is nearly all empty
@@ -420,7 +433,7 @@ __global__ __launch_bounds__(kThreads, wgs_per_cu(D)) void paged_attn_kernel(
     koff[i] = uint32_t(key_row(m) * kRowBytes + k_slot<D>(m, lane % kKch) * 16 + 1024 - i * 1024);
   }
   const uint32_t voff = uint32_t((lane >> 1) * 32 + v_slot(lane >> 1, lane & 1) * 16);
-  const uint32_t ring0 = lds_offset(ring) + wave * kSlabBytes;  // this wave's quarter of K tile 0
+  const uint32_t ring0 = lds_offset(ring) + blk * kSlabBytes;  // this wave's quarter of K tile 0
 
   // By position: this workgroup's next place in its queue, the end of that
   // part, the step to the place after; then what is left for the counter.
@@ -463,18 +476,20 @@ __global__ __launch_bounds__(kThreads, wgs_per_cu(D)) void paged_attn_kernel(
   unsigned w = next_static();
 
   // Columns are split into (query row, head of the group) by a 16-bit
-  // reciprocal of G: exact for the offsets met here, below G + 128 <= 192
+  // reciprocal of G: exact for the offsets met here, below G + kCols <= 320
   // (u * (65536 / G + 1 - 65536 / G exactly) < u * G / 65536 < 1 / G).
   const unsigned recip = 65536u / unsigned(G) + 1u;
   auto div_g = [&](int u) { return int((unsigned(u) * recip) >> 16); };
 
   // State of the item whose loads were last started ...
   int kvh = 0, row0 = 0, rem0 = 0;  // kv head; query row and head of its first column
-  int n_valid = 0;                  // its query columns (up to 128)
+  int n_valid = 0;                  // its query columns (up to kCols)
   int n_tiles = 0, key_lim = 0, n_blk_used = 0, wave_last = -1, wave_pos_min = 0, t0 = 0;
   int pos = 0, my_ord = 0, my_pos = 0;  // of this lane's column
   bool wave_active = false;
   const int32_t* bt = block_tables;
+  int c_r = 0;                       // COUNTED: the item's request (the next one's, mostly),
+  unsigned c_base = 0, c_tiles = 0;  // the column tiles before it, and its own
   int id_next = 0, raw_next = 0;  // block id of the next tile to issue V of, raw id of the one after
   const int T_s = kv_split / kKeys;  // kFused: tiles every request shares (at least 3)
   const uint64_t kbase0 = reinterpret_cast<uint64_t>(k_pool) - 1024, vbase0 = reinterpret_cast<uint64_t>(v_pool);
@@ -496,22 +511,22 @@ __global__ __launch_bounds__(kThreads, wgs_per_cu(D)) void paged_attn_kernel(
 #pragma unroll
   for (int i = 0; i < kDt; ++i) asm volatile("" : "=v"(o[i]));
 
-  auto raw_id = [&](int tl) { return scalar_load(bt + min((t0 + tl) * kTileBlocks + wave, max_blocks - 1)); };
+  auto raw_id = [&](int tl) { return scalar_load(bt + min((t0 + tl) * kTileBlocks + blk, max_blocks - 1)); };
   // Pool block of this wave in tile tl, from the raw table entry; unusable
   // ids read block 0 instead (stray K rows only meet masked scores, stray V
   // rows past key_lim are zeroed below).
   auto usable = [&](int tl, int id) {
     if constexpr (kIsFused) return (id >= 0 && id < num_blocks) ? id : 0;
-    return ((t0 + tl) * kTileBlocks + wave < n_blk_used && id >= 0 && id < num_blocks) ? id : 0;
+    return ((t0 + tl) * kTileBlocks + blk < n_blk_used && id >= 0 && id < num_blocks) ? id : 0;
   };
-  auto buf = [&](int tl) { return (unsigned(tbase + tl) & 1u) * kTileBytes; };
+  auto buf = [&](int tl) { return (unsigned(tbase + tl) % unsigned(kBufs)) * kTileBytes; };
   auto slab_at = [&](int id) { return size_t(id) * slab_stride + size_t(kvh) * kSlabBytes; };
   auto issue_k = [&](int tl, int id) { load_slab<kInsts>(koff, kbase0 + slab_at(id), ring0 + buf(tl)); };
   auto issue_v = [&](int tl, int id) {
-    load_slab_linear<kInsts>(voff, vbase0 + slab_at(id), ring0 + 2 * kTileBytes + buf(tl));
+    load_slab_linear<kInsts>(voff, vbase0 + slab_at(id), ring0 + kBufs * kTileBytes + buf(tl));
   };
   auto k_at = [&](int tl) { return ring + buf(tl); };
-  auto v_at = [&](int tl) { return ring + 2 * kTileBytes + buf(tl); };
+  auto v_at = [&](int tl) { return ring + kBufs * kTileBytes + buf(tl); };
   // Element offset in q / out of the row of column offset co of an item.
   auto row_of = [&](int r0, int m0, int h, int co) {
     const int u = m0 + co, t = div_g(u);
@@ -531,29 +546,32 @@ __global__ __launch_bounds__(kThreads, wgs_per_cu(D)) void paged_attn_kernel(
       // then the 32 behind it.
       const unsigned at = w / unsigned(Hkv);
       constexpr int kStride = kIndex / 64;
-      const int blk = __popcll(__ballot(first_tile[min(lane * kStride, n_groups)] <= at)) - 1;
-      const bool here = lane < kStride && first_tile[min(blk * kStride + lane, n_groups)] <= at;
-      const int g = blk * kStride + __popcll(__ballot(here)) - 1;
-      r = g << count_shift;
-      unsigned base = __builtin_amdgcn_readfirstlane(first_tile[g]);
-      unsigned tiles = __builtin_amdgcn_readfirstlane(first_tile[g + 1]) - base;
-      if (count_shift > 0) {  // which of the group's requests (at most 64)
-        const bool in = lane < (1 << count_shift) && r + lane < n_req;
-        const unsigned t = in ? tiles_of(r + lane) : 0u;
-        unsigned sum = t;
+      if (at - c_base >= c_tiles) {
+        const int blk = __popcll(__ballot(first_tile[min(lane * kStride, n_groups)] <= at)) - 1;
+        const bool here = lane < kStride && first_tile[min(blk * kStride + lane, n_groups)] <= at;
+        const int g = blk * kStride + __popcll(__ballot(here)) - 1;
+        c_r = g << count_shift;
+        c_base = __builtin_amdgcn_readfirstlane(first_tile[g]);
+        c_tiles = __builtin_amdgcn_readfirstlane(first_tile[g + 1]) - c_base;
+        if (count_shift > 0) {  // which of the group's requests (at most 64)
+          const bool in = lane < (1 << count_shift) && c_r + lane < n_req;
+          const unsigned t = in ? tiles_of(c_r + lane) : 0u;
+          unsigned sum = t;
 #pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-          const unsigned v = __shfl_up(sum, off);
-          sum += lane >= off ? v : 0u;
+          for (int off = 1; off < 64; off <<= 1) {
+            const unsigned v = __shfl_up(sum, off);
+            sum += lane >= off ? v : 0u;
+          }
+          const int l = __popcll(__ballot(c_base + sum <= at));  // requests that end at or before it
+          c_tiles = __builtin_amdgcn_readlane(t, l);
+          c_base += __builtin_amdgcn_readlane(sum, l) - c_tiles;
+          c_r += l;
         }
-        const int l = __popcll(__ballot(base + sum <= at));  // requests that end at or before it
-        tiles = __builtin_amdgcn_readlane(t, l);
-        base += __builtin_amdgcn_readlane(sum, l) - tiles;
-        r += l;
       }
-      const unsigned in_r = w - base * unsigned(Hkv);
-      kvh = int(in_r / tiles);
-      tile = int(tiles - 1u - in_r % tiles);
+      r = c_r;
+      const unsigned in_r = w - c_base * unsigned(Hkv);
+      kvh = int(in_r / c_tiles);
+      tile = int(c_tiles - 1u - in_r % c_tiles);
     } else {
       tile = kIsFused ? int(w % unsigned(n_col_tiles)) : n_col_tiles - 1 - int(w % unsigned(n_col_tiles));
       const unsigned rest = w / unsigned(n_col_tiles);
@@ -611,9 +629,11 @@ __global__ __launch_bounds__(kThreads, wgs_per_cu(D)) void paged_attn_kernel(
                     : (pos0 + div_g(rem0 + min(wave_first + kColsPerWave, n_valid) - 1)) / kKeys - t0;
     const int id0 = usable(0, raw_id0);
     id_next = usable(1, raw_id1);
-    issue_k(0, id0);
-    issue_v(0, id0);
-    if (1 < n_tiles) issue_k(1, id_next);
+    if (!lag) {
+      issue_k(0, id0);
+      issue_v(0, id0);
+      if (1 < n_tiles) issue_k(1, id_next);
+    }
     const size_t qrow = row_of(row0, rem0, kvh, co);
 #pragma unroll
     for (int kc = 0; kc < kDch; ++kc) qf[kc] = as_bf16x8(*(const u32x4*)(q + qrow + kc * 16 + hh * 8));
@@ -678,9 +698,9 @@ __global__ __launch_bounds__(kThreads, wgs_per_cu(D)) void paged_attn_kernel(
   // starting at key j0 (the wave's own loads of it have landed; the other
   // waves read it only after the next barrier).
   auto zero_v_tail = [&](int tl, int j0, int lim) {
-    const int nv_blk = lim - (j0 + wave * kBlock);
+    const int nv_blk = lim - (j0 + blk * kBlock);
     if (nv_blk >= kBlock) return;
-    uint8_t* sV = v_at(tl) + wave * kSlabBytes;
+    uint8_t* sV = v_at(tl) + blk * kSlabBytes;
     const int nvalid = nv_blk - v_slot(lane >> 1, lane & 1) * 8;
 #pragma unroll
     for (int i = 0; i < kInsts; ++i) {
@@ -958,6 +978,19 @@ __global__ __launch_bounds__(kThreads, wgs_per_cu(D)) void paged_attn_kernel(
   // of the stores until the next item's B_0 (each wave its own quarter, which
   // only its own loads write).  The fused list is read only before B_{n-1},
   // the item word between B_{n-1} and the next S.
+  //   kWide: both halves of the workgroup run the stream M_0, V_0, M_1, V_1, ...,
+  // and meet in the same barriers, but waves 0-3 pass B_j before V_j and waves
+  // 4-7 (lag) before M_j: between two barriers one half does V_j, M_{j+1}, the
+  // other M_j, V_j, so that on every SIMD one wave's softmax meets the other's
+  // products (at an item's end the lagging half's last products, and its store,
+  // follow S).  A tile is read over two such intervals, so K and V have three
+  // buffers each: behind B_j, K(j+2) takes the buffer of K(j-1), whose last
+  // reader, the lagging half's M_{j-1}, ended before B_j, and V(j+1) that of
+  // V(j-2), read with it; the next item's K(0), K(1) and V(0), issued after
+  // B_{n-1}, those of K(n-3), K(n-2) and V(n-3).  Stores go through V(n-2)'s
+  // buffer (waves 0-3) and K(n-1)'s (waves 4-7), free between S and B_0.  Waves
+  // 0-3 issue all loads, in their softmax phase: issued by the lagging half in
+  // front of its products, its share cost 8% of the launch.
   auto ask = [&]() {  // (nothing is in flight)
     __syncthreads();
     if (tid == 0) {
@@ -980,15 +1013,20 @@ __global__ __launch_bounds__(kThreads, wgs_per_cu(D)) void paged_attn_kernel(
   if (!started) break;
   bool have_prev = false;  // a finished item's O is still to be stored
   int p_row0 = 0, p_rem0 = 0, p_kvh = 0, p_valid = 0;
+  bool act = false;
+  const uint8_t* v_last = ring;
+  // Transpose area of the stores.
+  auto store_area = [&]() { return (kWide && lag ? k_at(2) : v_at(1)) + blk * kSlabBytes; };
   for (;;) {
-    wait_vmcnt<0>();
+    if (!lag) wait_vmcnt<0>();
     bare_barrier();  // S
+    if (lag && have_prev && act) m_phase(yes(), no(), v_last, ring);
     if constexpr (kIsFused) n_tiles = T_s + __builtin_amdgcn_readfirstlane(f_count);
     // The next item: a number is asked for here and read after B_{n-1}.
     w = next_static();
     unsigned ticket = 0;
     if (tid == 0 && w == kAsk && qsel < 8u) ticket = take();
-    if (have_prev) store_item(p_row0, p_rem0, p_kvh, p_valid, v_at(1) + wave * kSlabBytes);
+    if (have_prev) store_item(p_row0, p_rem0, p_kvh, p_valid, store_area());
     if (w == kAsk && tid == 0) {
       s_item = resolve(ticket);
       wait_lgkmcnt0();
@@ -1029,8 +1067,10 @@ __global__ __launch_bounds__(kThreads, wgs_per_cu(D)) void paged_attn_kernel(
       if constexpr (kIsFused) return wave_active && (tl < T_s || (ord >= ord_lo && ord <= ord_hi));
       return tl <= wave_last;
     };
-    bool act = wave_active;
-    if (act) m_phase(no(), yes(), ring, k_at(0));
+    act = wave_active;
+    if constexpr (!kWide) {
+      if (act) m_phase(no(), yes(), ring, k_at(0));
+    }
     int cur_ord = 0, cur_tt = 0;  // kFused: request number and tile of item tile j (a shared one: itself)
     int j0 = t0 * kKeys, thr = INT_MAX, next_ord = 0, next_tt = 0;
     // First key and (kFused) mask threshold of tile j, and the zeroing of its V tail.
@@ -1048,10 +1088,41 @@ __global__ __launch_bounds__(kThreads, wgs_per_cu(D)) void paged_attn_kernel(
         if (j + 1 >= T_s && j + 1 < n_tiles) fused_entry(j + 1, next_ord, next_tt);
       } else {
         j0 = (t0 + j) * kKeys;
-        if (j0 + kKeys > key_lim) zero_v_tail(j, j0, key_lim);
+        if (!lag && j0 + kKeys > key_lim) zero_v_tail(j, j0, key_lim);
       }
     };
-    for (int j = 0;; ++j) {
+    if constexpr (kWide) {
+      auto barrier = [&](int j) {  // B_j, and the loads behind it
+        if (!lag && j > 0) wait_vmcnt<0>();
+        before_barrier(j);
+        bare_barrier();
+        if (!lag && j + 1 < n_tiles) {
+          issue_v(j + 1, id_next);
+          if (j + 2 < n_tiles) {
+            id_next = usable(j + 2, raw_next);
+            issue_k(j + 2, id_next);
+          }
+        }
+      };
+      if (lag) barrier(0);
+      if (act) m_phase(no(), yes(), ring, k_at(0));
+      if (!lag) barrier(0);
+      for (int j = 0; j < n_tiles - 1; ++j) {
+        if (!lag && j + 3 < n_tiles) raw_next = raw_id(j + 3);
+        int jj = j;
+        asm volatile("" : "+s"(jj));
+        if (act) {
+          mask(j0, thr);
+          softmax(MODE != kSuffix && jj == 0);
+        }
+        asm volatile("" : "+s"(raw_next));
+        if (lag) barrier(j + 1);
+        if (act) m_phase(yes(), yes(), v_at(j), k_at(j + 1));
+        if (!lag) barrier(j + 1);
+        act = active(j + 1, 0);
+      }
+    }
+    for (int j = 0; !kWide; ++j) {
       if (j > 0) wait_vmcnt<0>();  // (tile 0's were waited for before S; only stores follow them)
       before_barrier(j);
       bare_barrier();  // B_j
@@ -1096,7 +1167,7 @@ __global__ __launch_bounds__(kThreads, wgs_per_cu(D)) void paged_attn_kernel(
     }
     if (act) mask(j0, thr);
     const bool first = MODE != kSuffix && n_tiles == 1;
-    const uint8_t* v_last = v_at(n_tiles - 1);
+    v_last = v_at(n_tiles - 1);
     tbase += n_tiles;
     p_row0 = row0;
     p_rem0 = rem0;
@@ -1107,12 +1178,16 @@ __global__ __launch_bounds__(kThreads, wgs_per_cu(D)) void paged_attn_kernel(
     if (!started && w != kNoItem) w = next_static();  // (an item without work)
     if (act) {
       softmax(first);
-      m_phase(yes(), no(), v_last, ring);
+      if (!lag) m_phase(yes(), no(), v_last, ring);
     }
     if (!started) break;
     have_prev = true;
   }
-  store_item(p_row0, p_rem0, p_kvh, p_valid, ring + wave * kSlabBytes);
+  if constexpr (kWide) {
+    bare_barrier();  // (S)
+    if (lag && act) m_phase(yes(), no(), v_last, ring);
+  }
+  store_item(p_row0, p_rem0, p_kvh, p_valid, kWide ? store_area() : ring + wave * kSlabBytes);
   }
 
   // (stealing) Every queue is drained.  The last workgroup out clears the
@@ -1254,16 +1329,17 @@ int check_attn_args(const char* fn, const uint16_t* q, const uint16_t* k_pool, c
 template <int MODE>
 int launch_attn(const char* fn, const uint16_t* q, const uint16_t* k_pool, const uint16_t* v_pool,
                 int32_t num_blocks, const int32_t* block_tables, int32_t max_blocks, const int32_t* cu_q,
-                const int32_t* seq_lens, int32_t B, int32_t Hq, int32_t Hkv, int32_t D, int64_t col_tiles,
+                const int32_t* seq_lens, int32_t B, int32_t Hq, int32_t Hkv, int32_t D, int64_t cols,
                 float scale_log2, uint16_t* out, unsigned* queue, int kv_split, float* part_o,
                 float* part_ml, int part_rows, hipStream_t s) {
-  const int64_t items = col_tiles * Hkv * (MODE == kShared || MODE == kFused ? 1 : B);
+  int64_t col_tiles = (cols + kCols - 1) / kCols;
+  int64_t items = col_tiles * Hkv * (MODE == kShared || MODE == kFused ? 1 : B);
   if (items == 0) return ILPC_OK;
   if (items >= int64_t(kAsk)) return ilpc::set_error(ILPC_EUNSUP, "%s: grid too large", fn);
   const int cus = ilpc::device_cus();
   if (cus <= 0) return ilpc::set_error(ILPC_EHIP, "%s: cannot query the device", fn);
   const int64_t wgs = int64_t(wgs_per_cu(D)) * cus;
-  const unsigned grid = unsigned(items < wgs ? items : wgs);
+  unsigned grid = unsigned(items < wgs ? items : wgs);
   // Chunks of the item numbers dealt to the XCDs' queues in turn: whole
   // (request, kv head) pairs, whose items read the same K/V, when they deal out
   // evenly (or nearly so), else pieces that do.
@@ -1280,24 +1356,46 @@ int launch_attn(const char* fn, const uint16_t* q, const uint16_t* k_pool, const
        (MODE == kFull && Hkv < 8 && col_tiles * 16 >= 5 * int64_t(grid) && items >= int64_t(kLongRounds / 2) * grid));
   int shift = 0;
   while (((B - 1) >> shift) + 1 > kIndex - 1) ++shift;
-  const unsigned chunk = unsigned(
+  unsigned chunk = unsigned(
       items >= int64_t(kLongRounds) * grid ? (items + 7) / 8
       : pairs % 8 == 0 || pairs >= 256     ? col_tiles
                                            : std::max<int64_t>(items / 256, 1));
+  unsigned threads = 64 * kWaves;
   auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), 0, s, q, k_pool, v_pool, num_blocks, block_tables, max_blocks,
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, s, q, k_pool, v_pool, num_blocks, block_tables, max_blocks,
                        cu_q, seq_lens, B, Hq, Hkv, int(col_tiles), unsigned(items), chunk, counted ? shift : -1,
                        scale_log2, out, queue, kv_split, part_o, part_ml, part_rows);
   };
   if constexpr (MODE == kFull || MODE == kSuffix) {
     if (counted) {
-      if (D == 128) launch(paged_attn_kernel<128, MODE, true>);
-      else launch(paged_attn_kernel<64, MODE, true>);
+      if constexpr (MODE == kFull) {
+        // Both layouts, of which the one that the batch's rows do not call for
+        // returns at once (2 to 3 us; only the device knows how many rows
+        // there are).  The wide one where the items fill its 256 columns -- 192
+        // or 256 columns a pair 8-14% faster, 512 and from 1024 on 5-8%, 320,
+        // 384 and 640 the same -- and give every CU eight of them: below, items
+        // half as large level better (64 requests of 1 row but one of 600, 32/8
+        // heads, 31 us narrow, 39 wide).
+        constexpr int kWideCols = 2 * kCols;
+        if (D == 128 && items >= int64_t(kLongRounds) * wgs && (cols >= 4 * kWideCols || (cols - 1) % kWideCols >= kCols)) {
+          part_rows = int(std::max<int64_t>(1, int64_t(kWideRounds) * kWideCols * cus / Hq));
+          const int64_t narrow_tiles = col_tiles, narrow_items = items;
+          const unsigned narrow_grid = grid;
+          col_tiles = (cols + kWideCols - 1) / kWideCols;
+          items = col_tiles * Hkv * B;
+          grid = unsigned(std::min<int64_t>(items, cus));
+          threads = 128 * kWaves;
+          launch(paged_attn_kernel<128, MODE, true, 2 * kWaves>);
+          col_tiles = narrow_tiles, items = narrow_items, grid = narrow_grid, threads = 64 * kWaves;
+        }
+      }
+      if (D == 128) launch(paged_attn_kernel<128, MODE, true, kWaves>);
+      else launch(paged_attn_kernel<64, MODE, true, kWaves>);
       return launch_status(fn);
     }
   }
-  if (D == 128) launch(paged_attn_kernel<128, MODE, false>);
-  else launch(paged_attn_kernel<64, MODE, false>);
+  if (D == 128) launch(paged_attn_kernel<128, MODE, false, kWaves>);
+  else launch(paged_attn_kernel<64, MODE, false, kWaves>);
   return launch_status(fn);
 }
 
@@ -1334,9 +1432,8 @@ extern "C" int ilpc_paged_prefill_attn(const uint16_t* q, const uint16_t* k_pool
   if (few_columns(B, max_q_len, Hq, Hkv, D, max_blocks))
     return ilpc::launch_decode_attn(q, k_pool, v_pool, num_blocks, block_tables, max_blocks, cu_q, seq_lens, B,
                                     max_q_len, Hq, Hkv, D, scale_log2, out, 1, true, nullptr, stream);
-  const int64_t col_tiles = (int64_t(max_q_len) * (Hq / Hkv) + kCols - 1) / kCols;
   return launch_attn<kFull>(fn, q, k_pool, v_pool, num_blocks, block_tables, max_blocks, cu_q, seq_lens, B,
-                            Hq, Hkv, D, col_tiles, scale_log2, out,
+                            Hq, Hkv, D, int64_t(max_q_len) * (Hq / Hkv), scale_log2, out,
                             static_cast<unsigned*>(workspace), 0, nullptr, nullptr, 0,
                             static_cast<hipStream_t>(stream));
 }
@@ -1421,7 +1518,7 @@ extern "C" int ilpc_paged_prefill_attn_cascade(
   const float scale_log2 = softmax_scale * 1.4426950408889634f;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int G = Hq / Hkv;
-  const int64_t col_tiles = (int64_t(max_q_len) * G + kCols - 1) / kCols;
+  const int64_t cols = int64_t(max_q_len) * G;
   // (few_columns() as in ilpc_paged_prefill_attn, whose pass shared_len = 0 runs;
   // with so few columns the sharing saves less than the idle CUs cost)
   if (!decode_shaped(max_q_len, Hq, Hkv) && few_columns(B, max_q_len, Hq, Hkv, D, max_blocks))
@@ -1429,7 +1526,7 @@ extern "C" int ilpc_paged_prefill_attn_cascade(
                                     max_q_len, Hq, Hkv, D, scale_log2, out, 1, true, nullptr, stream);
   if (shared_len == 0)
     return launch_attn<kFull>(fn, q, k_pool, v_pool, num_blocks, block_tables, max_blocks, cu_q, seq_lens,
-                              B, Hq, Hkv, D, col_tiles, scale_log2, out, queue_shared, 0, nullptr, nullptr,
+                              B, Hq, Hkv, D, cols, scale_log2, out, queue_shared, 0, nullptr, nullptr,
                               0, s);
   // One launch (kFused) for prefill-shaped batches whose shared prefix holds
   // at least three 64-key tiles and whose per-item tile list fits: at most
@@ -1440,13 +1537,13 @@ extern "C" int ilpc_paged_prefill_attn_cascade(
   if (T_s >= 3 && int64_t(max_q_len) * G >= 2 * kColsPerWave &&
       ((kCols + G - 1) / G + 1) * own_tiles <= kFusedTiles)
     return launch_attn<kFused>(fn, q, k_pool, v_pool, num_blocks, block_tables, max_blocks, cu_q, seq_lens, B,
-                               Hq, Hkv, D, (rows * G + kCols - 1) / kCols, scale_log2, out, queue_shared,
+                               Hq, Hkv, D, rows * G, scale_log2, out, queue_shared,
                                int(T_s * kKeys), nullptr, nullptr, int(rows), s);
   rc = launch_attn<kShared>(fn, q, k_pool, v_pool, num_blocks, block_tables, max_blocks, cu_q, seq_lens, B,
-                            Hq, Hkv, D, (rows * G + kCols - 1) / kCols, scale_log2, out, queue_shared,
+                            Hq, Hkv, D, rows * G, scale_log2, out, queue_shared,
                             shared_len, part_o, part_ml, int(rows), s);
   if (rc != ILPC_OK) return rc;
   return launch_attn<kSuffix>(fn, q, k_pool, v_pool, num_blocks, block_tables, max_blocks, cu_q, seq_lens, B,
-                              Hq, Hkv, D, col_tiles, scale_log2, out, queue_suffix, shared_len, part_o,
+                              Hq, Hkv, D, cols, scale_log2, out, queue_suffix, shared_len, part_o,
                               part_ml, int(rows), s);
 }

@@ -2,7 +2,7 @@
 workspace left zeroed, for launches that take their items by position only, by
 position and through the queues' counters, and (many items per workgroup)
 through the counters with helping between queues; with few of the item numbers
-holding work, which long launches count before they start.
+holding work, which long launches count before they start; and in the wide layout.
 
 The reference is the same batch in small launches of one item per workgroup
 (checked against the fp64 oracle elsewhere): a query row meets the same keys in
@@ -27,6 +27,10 @@ BLOCK = 16
     (64, 8, 4, 197, 30, 50),     # head size 64: three workgroups per CU
     (64, 12, 4, 40, 400, 60),
     (64, 4, 1, 12400, 20, 20),
+    (128, 32, 8, 80, 700, 200),  # the wide layout: 256-column items
+    (128, 28, 4, 150, 600, 60),  # a group of 7
+    (128, 64, 8, 700, 32, 0),    # one tile an item
+    (128, 64, 8, 336, 64, 12000),  # up to 189 tiles
 ])
 def test_every_item_once(D, Hq, Hkv, B, q_max, P_max):
     rng = np.random.default_rng(B)
@@ -55,6 +59,18 @@ def test_numbers_without_work(D, Hq, Hkv, B, long, n_long, short):
     q_len[rng.permutation(B)[:n_long]] = long
     q_len[-1] = long if B % 2 else q_len[-1]
     _check(D, Hq, Hkv, q_len, 40, rng, q_max=long or 1500)
+
+
+@pytest.mark.parametrize("short", [1, 0])
+def test_rows_on_both_sides_of_the_wide_layouts_line(short):
+    """Eight 256-column items a CU: as many rows, and one fewer."""
+    Hq, B = 32, 64
+    line = 8 * 256 * torch.cuda.get_device_properties(0).multi_processor_count // Hq
+    q_len = np.full(B, (line - 512) // (B - 1))
+    q_len[7] = 512                       # 64 x 8 x 16 numbers: a long launch
+    q_len[9] += line - q_len.sum() - short
+    assert q_len.sum() == line - short
+    _check(128, Hq, 8, q_len, 300, np.random.default_rng(short), q_max=512)
 
 
 def _check(D, Hq, Hkv, q_len, P_max, rng, q_max=None):

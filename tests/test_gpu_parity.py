@@ -431,15 +431,14 @@ def test_work_queue_workspace_reused_and_left_zeroed():
     assert int(ilpc.attn_workspace(None, side).count_nonzero()) == 0
 
 
-@pytest.mark.parametrize("n_prompts", [1, 3, 7, 9, 13, 260, 300])
+@pytest.mark.parametrize("n_prompts", [1, 3, 7, 9, 13, 260, 300, 800, 1900])
 def test_item_assignment_and_queue_reset(n_prompts):
-    """tiny gives one work item per request.  Up to the number of compute
-    units, every workgroup takes one item by position (fewer items than
-    queues, uneven queues); 260 and 300 items go through the queues, where
-    the workgroups left after the first round take the remaining items from
-    other XCDs' queues or stop on the drained-queue count.  Every request
-    matches the oracle, twice in a row on one workspace, and the workspace is
-    left zero-filled."""
+    """tiny gives one work item per request.  Up to the number of workgroups
+    (three a compute unit at head size 64: 768) each takes one item by position,
+    fewer items than queues and uneven queues among them; of 800 and 1900 the
+    last round goes through the queues' counters, which each queue's last asker
+    clears.  Every request matches the oracle, twice in a row on one workspace,
+    and the workspace is left zero-filled."""
     run = Run(workload.scaled_spec("tiny", n_prompts))
     b, pc, q, scale = run.batch, run.pc, run.rows["q"], run.wl.spec.scale
     ws = torch.zeros(64, dtype=torch.uint8, device="cuda")
@@ -550,7 +549,7 @@ def test_cascade_decode_steps_against_oracle():
 @pytest.mark.parametrize("q_pattern", ["ragged", "small", "with_empty"])
 def test_cascade_fused_many_requests_per_item(q_pattern):
     # Prefill-shaped cascades with at least three shared 64-key tiles run as
-    # one launch whose items are 256 columns of the whole batch: here each
+    # one launch whose items are 128 columns of the whole batch: here each
     # request keeps only its last k queries (k ragged, small so that one item
     # spans up to 64 requests, or zero for some requests), so items mix many
     # requests and request tiles are masked to their own columns.

@@ -90,8 +90,18 @@ def test_head_groups(G, Hkv, D):
 
 def test_long_context_twelve_thousand_keys():
     # each prompt's own 11 968-token prefix is cached; 1..100 new tokens follow
+    # (72 column tiles of 32: the decode kernel)
     spec = workload.WorkloadSpec(name="long12k", n_q_heads=8, n_kv_heads=1, head_dim=128, n_prompts=3,
                                  instr_len=0, n_demos=187, demo_len=64, pool_size=200, query_len=(1, 100),
+                                 warm="own_prefix", own_prefix_len=11968, seed=700)
+    c = _run_and_check(spec)
+    assert (c == 11968).all()
+
+
+def test_long_context_on_the_persistent_kernel():
+    # four kv heads: more column tiles (288 of 32) than the decode kernel takes
+    spec = workload.WorkloadSpec(name="long12k_h4", n_q_heads=32, n_kv_heads=4, head_dim=128, n_prompts=3,
+                                 instr_len=0, n_demos=187, demo_len=64, pool_size=200, query_len=(89, 100),
                                  warm="own_prefix", own_prefix_len=11968, seed=700)
     c = _run_and_check(spec)
     assert (c == 11968).all()
