@@ -466,19 +466,37 @@ size_t decode_split_bytes(int B, int max_q_len, int Hq, int Hkv, int D, int n_sp
 //
 // A CU takes in about 58 GB/s whatever runs on it (8000 keys, D 128, us: one
 // workgroup of four waves 71.7, of eight 72.3), so what shortens a long context
-// is CUs.  Waves double up to four, one workgroup, as long as every workgroup has
-// a CU to itself: beyond, some CUs get two and the launch waits for them (us, 800
-// keys: 264 pairs by two 20.4, by four 26.0; 576 pairs by one 35.8, by two 46.7,
-// by four 40.0); column tiles of one pair, which read the same keys, take two
-// workgroups to a CU at D = 64 (512 of them, 16 K keys: by two 167, by four 147).
-// Eight gain only at D = 64 where a pair has one workgroup and 24 steps or more
-// (4 requests, 2 kv heads, 16 K keys 86.5 -> 73.8; 64 of 800 8.9 -> 8.2).
+// is CUs, and what the launch waits for is the CUs with most to do.  Four waves
+// to a pair, a workgroup of its own, as long as each has a CU to itself (at
+// D = 64, whose steps and merge are shorter, two pairs to a CU).  Then two, up to
+// four pairs to a CU, where all workgroups run at once; and four again, quarters
+// of the load, where twos or whole pairs leave some CUs twice the work of others:
+// up to half as many pairs again as two (four) to a CU, from 8 (32) steps on,
+// where the merges pay.  8 kv heads, D 128, contexts of 0.85 to 1 of these
+// lengths, unshared and (60% of the keys shared by all requests), us by one, two,
+// four:
+//   320 pairs of 2400 keys   118, 70.7, 80.1 (86.0, 46.0, 50.1)
+//   512 of 1056              42.2, 40.9, 41.0 (41.3, 24.7, 24.8)
+//   576 of 300               16.9, 21.0, 18.8 (15.6, 16.4, 14.9)
+//   576 of 1000              47.4, 57.3, 48.8 (40.4, 39.9, 31.9)
+//   768 of 800               46.1, 50.8, 45.9 (35.9, 33.1, 27.9)
+//   800 of 1056              75.8, 80.9, 81.5 (46.7, 42.6, 42.3)
+//   1024 of 1056             95.4, 95.1, 95.6 (53.6, 43.7, 45.0)
+//   1248 of 2000             277, 242, 226  (of 2400: 211, 163, 146)
+//   1536 of 2000             302, 274, 277  (of 2400: 215, 177, 177)
+// D 64, 4 kv heads: 264 of 300 9.3, 6.9, 6.5; 320 of 1056 27.0, 17.0, 17.6 (25.9,
+// 15.4, 13.5); 600 of 500 16.0, 16.9, 15.1 (14.0, 13.0, 11.0).  Eight gain only
+// at D = 64 where a pair has one workgroup (4 requests, 2 kv heads, 16 K keys
+// 86.5 -> 73.8; 64 of 800 8.9 -> 8.2; not on few pairs of that many: 20 of 830
+// keys 7.5 -> 7.8).
 //
 // A wave's steps follow each other at about 1 us (D = 64: 0.55) and the second
 // launch costs 3 to 3.5 us, so workgroups are added -- one to a CU, at most 16 --
 // where they take kGain steps off every wave, and no more of them than keep that
-// step count; below three to a pair (over 85 pairs) the reads are the bound and
-// two pay only past 128 steps.  us, one workgroup -> this rule, 8 kv heads, D 128
+// step count; at D = 64 from 32 steps on (26 steps: 7.5 -> 7.7, and 10.9 -> 12.7
+// for a step issued with its append, where the host's third launch shows); below
+// three to a pair (over 85 pairs) the reads are the bound and two pay only past
+// 128 steps.  us, one workgroup -> this rule, 8 kv heads, D 128
 // (D 64 with 2 kv heads): 1 request of 604 keys 9.2 -> 8.5, of 8000 71.7 -> 13.2;
 // 4 of 1000 12.8 -> 8.7 (8.2 -> 7.2), of 2100 22.9 -> 12.4, of 4000 38.5 -> 16.9
 // (22.1 -> 8.3); 8 of 2100 23.4 -> 17.2; 16 of 8000 110.8 -> 95.3; left at one
@@ -487,19 +505,21 @@ struct Plan {
   int waves, groups;
 };
 
-static Plan decode_plan(int64_t pairs, bool tiles, int64_t steps, int D, int64_t n_max, int64_t least) {
-  const int64_t cus = device_cus(), per_cu = D == 64 && tiles ? 2 : 1;
-  int64_t w = 1, n = 1;
-  while (w < 4 && steps >= 2 * w && pairs * w * 2 <= 4 * per_cu * cus) w *= 2;
+static Plan decode_plan(int64_t pairs, int64_t steps, int D, int64_t n_max, int64_t least) {
+  const int64_t cus = device_cus();
+  const bool four = pairs <= (D == 64 ? 2 : 1) * cus || (pairs > 2 * cus && pairs <= 3 * cus && steps >= 8) ||
+                    (pairs > 4 * cus && pairs <= 6 * cus && steps >= 32);
+  int64_t w = four ? 4 : pairs <= 4 * cus ? 2 : 1, n = 1;
+  while (w > steps) w /= 2;
   if (w == 4 && cus / pairs >= 3) {
     const int64_t room = std::min<int64_t>({cus / pairs, n_max, kMaxGroups});
     const int64_t alone = (steps + 3) / 4, each = (alone + room - 1) / room;  // steps a wave
     const int64_t kGain = D == 64 ? 6 : 4;
-    if (alone - each >= kGain) n = (steps + 4 * each - 1) / (4 * each);
+    if (alone - each >= kGain && (D == 128 || steps >= 32)) n = (steps + 4 * each - 1) / (4 * each);
   } else if (w == 4 && cus / pairs == 2 && n_max >= 2 && steps > 128) {
     n = 2;
   }
-  if (D == 64 && w == 4 && n == 1 && steps >= 24 && pairs <= cus) w = 8;
+  if (D == 64 && w == 4 && n == 1 && pairs <= cus && steps >= (cus / pairs >= 3 ? 32 : 24)) w = 8;
   // More ranges asked for (up to one a step): one workgroup of eight waves if
   // that is enough, else of four while they have a CU each (us, 1 request of 400
   // keys, 8 kv heads: 8 ranges as 1 x 8 8.4, 2 x 4 9.1; 16 as 2 x 8 9.8, 4 x 4
@@ -538,7 +558,7 @@ int launch_decode_attn(const uint16_t* q, const uint16_t* k_pool, const uint16_t
   const int cols_cap = int(std::min<int64_t>(all_cols, 32));
   const int64_t pairs = int64_t(B) * Hkv * n_ct;
   const int64_t steps = (int64_t(max_blocks) * kBlock + kStepKeys - 1) / kStepKeys;
-  const Plan plan = decode_plan(pairs, n_ct > 1, steps, D, n_split, automatic ? 1 : n_split);
+  const Plan plan = decode_plan(pairs, steps, D, n_split, automatic ? 1 : n_split);
   const int w = plan.waves;
   n_split = plan.groups;
   if (n_split > 1 && !part) return set_error(ILPC_EINVAL, "decode attention: no room for partial results");

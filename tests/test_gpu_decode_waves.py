@@ -17,12 +17,23 @@ BLOCK = 16
 @pytest.mark.parametrize("D,Hq,Hkv,B,L_max,rows,n_split", [
     (128, 8, 8, 300, 100, 1, 1),     # 2400 pairs: one wave each
     (128, 32, 8, 131, 70, 1, 1),     # 1048 pairs: one
+    (128, 8, 8, 128, 70, 1, 1),      # 1024: two, the most
+    (128, 8, 8, 129, 1010, 1, 1),    # 1032, 32 steps: four
+    (64, 8, 8, 192, 1010, 1, 1),     # 1536: four, the most
+    (64, 8, 8, 193, 1010, 1, 1),     # 1544: one
     (128, 64, 8, 33, 300, 1, 1),     # 264: two
     (128, 64, 8, 64, 70, 1, 1),      # 512: two, the most pairs
     (128, 64, 8, 32, 300, 1, 1),     # 256: four, the most pairs
     (128, 28, 4, 9, 33, 4, 1),       # 2 steps: two waves, 28 columns
     (64, 32, 2, 5, 20, 2, 1),        # 1 step, 32 columns: one wave
-    (64, 12, 4, 70, 500, 1, 1),
+    (64, 12, 4, 70, 500, 1, 1),      # 280: four at D 64
+    (64, 8, 8, 64, 100, 1, 1),       # 512: four at D 64
+    (64, 8, 8, 65, 230, 1, 1),       # 520, 8 steps: four
+    (128, 8, 8, 65, 220, 1, 1),      # 7 steps: two
+    (128, 8, 8, 96, 300, 1, 1),      # 768: four, the most before 1024
+    (128, 8, 8, 97, 300, 1, 1),      # 776: two
+    (128, 8, 8, 99, 30, 1, 1),       # 1 step: one
+    (128, 8, 8, 60, 100, 1, 1),      # 4 steps: two
     (128, 8, 8, 5, 200, 3, 2),       # 2 to 4 ranges: one workgroup a pair, no second launch
     (128, 32, 8, 5, 200, 1, 4),
     (128, 32, 8, 5, 400, 2, 5),      # one workgroup of eight waves
@@ -96,8 +107,9 @@ def test_the_persistent_kernel_past_the_line(D, Hq, Hkv, B, rows):
 @pytest.mark.parametrize("D,Hq,Hkv,B,L_max,rows", [
     (128, 64, 8, 4, 512, 1),         # 16 steps: one workgroup a pair
     (128, 64, 8, 4, 528, 1),         # 17: five of them
-    (64, 16, 2, 4, 768, 1),          # D 64, 24 steps: one, of eight waves
-    (64, 16, 2, 4, 784, 1),          # 25: seven of four
+    (64, 16, 2, 4, 992, 1),          # D 64, 31 steps: one
+    (64, 16, 2, 4, 1008, 1),         # 32: eight of four
+    (64, 4, 4, 25, 768, 1),          # 100 pairs, 24 steps: one, of eight waves
     (128, 64, 8, 4, 992, 1),
     (128, 64, 8, 4, 993, 1),
     (64, 16, 2, 1, 1300, 4),         # 41 steps in eleven, some ranges past the shorter rows' last key
@@ -171,33 +183,49 @@ def test_long_contexts_take_several_compute_units():
     """One CU takes in a pair's keys at its own rate, whatever the number of its
     waves: ranges have to go to other CUs (measured at 8000 keys: 0.18 and 0.24 of
     the time of one workgroup a pair; all ranges in one workgroup: 1.0)."""
-    Hq, Hkv, D, L = 32, 8, 128, 8000
     for B, n_split, share in ((1, 0, 0.22), (2, 8, 0.5)):
-        us = []
-        for n in (1, n_split):
-            kp, vp = (torch.randn(s, device="cuda", dtype=torch.bfloat16)
-                      for s in ((B * L // BLOCK, Hkv, BLOCK, D), (B * L // BLOCK, Hkv, D, BLOCK)))
-            bt = torch.arange(B * L // BLOCK, dtype=torch.int32, device="cuda").view(B, -1)
-            cu = torch.arange(B + 1, dtype=torch.int32, device="cuda")
-            Ls = torch.full((B,), L, dtype=torch.int32, device="cuda")
-            q = torch.randn(B, Hq, D, device="cuda", dtype=torch.bfloat16)
-            out = torch.empty_like(q)
-            ws = torch.zeros(ilpc.decode_workspace_bytes(B, 1, Hq, Hkv, D, 64), dtype=torch.uint8, device="cuda")
-            stream, graph, times = torch.cuda.Stream(), torch.cuda.CUDAGraph(), []
-            torch.cuda.synchronize()
-            with torch.cuda.graph(graph, stream=stream):
-                for _ in range(50):
-                    ilpc.paged_decode_attn(q, kp, vp, bt, cu, Ls, 1, D ** -0.5, out, stream, n, ws)
-            for _ in range(7):
-                ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
-                ev[0].record()
-                graph.replay()
-                ev[1].record()
-                torch.cuda.synchronize()
-                times.append(ev[0].elapsed_time(ev[1]) * 20)
-            us.append(sorted(times)[3])
-        print(f"[decode] {B} x {L} keys: one workgroup a pair {us[0]:.1f} us, n_split {n_split} {us[1]:.1f} us", flush=True)
+        us = [_time([8000] * B, n) for n in (1, n_split)]
+        print(f"[decode] {B} x 8000 keys: one workgroup a pair {us[0]:.1f} us, n_split {n_split} {us[1]:.1f} us", flush=True)
         assert us[1] <= share * us[0]
+
+
+@pytest.mark.parametrize("few,many,low,ratio", [
+    (128, 156, 2000, 1.4),           # 1024 pairs, two rounds of whole ones on half of the CUs; 1248 (1.54 by whole pairs, 1.27)
+    (64, 72, 1000, 1.3),             # 512 and 576 pairs of 1000 to 2000 keys (1.42 by whole pairs, 1.19)
+])
+def test_more_pairs_than_come_out_even(few, many, low, ratio):
+    """Where whole pairs would leave some CUs twice the work of others, or the
+    longest contexts alone at the end, waves share a pair: the time grows about
+    as the keys do (1.22 and 1.13)."""
+    us = [_time(np.random.default_rng(B).permutation(np.linspace(low, 2000, B).astype(np.int32)), 0) for B in (few, many)]
+    print(f"[decode] {few} and {many} requests of {low} to 2000 keys: {us[0]:.1f} and {us[1]:.1f} us", flush=True)
+    assert us[1] <= ratio * us[0]
+
+
+def _time(L, n_split):
+    """us of a decode step, contexts L, 32 / 8 heads of 128, in a replayed graph."""
+    Hq, Hkv, D, B, W = 32, 8, 128, len(L), -(-int(max(L)) // BLOCK)
+    kp, vp = (torch.randn(s, device="cuda", dtype=torch.bfloat16)
+              for s in ((B * W, Hkv, BLOCK, D), (B * W, Hkv, D, BLOCK)))
+    bt = torch.arange(B * W, dtype=torch.int32, device="cuda").view(B, -1)
+    cu = torch.arange(B + 1, dtype=torch.int32, device="cuda")
+    Ls = torch.tensor(np.asarray(L, np.int32), device="cuda")
+    q = torch.randn(B, Hq, D, device="cuda", dtype=torch.bfloat16)
+    out = torch.empty_like(q)
+    ws = torch.zeros(max(64, ilpc.decode_workspace_bytes(B, 1, Hq, Hkv, D, 64)), dtype=torch.uint8, device="cuda")
+    stream, graph, times = torch.cuda.Stream(), torch.cuda.CUDAGraph(), []
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=stream):
+        for _ in range(50):
+            ilpc.paged_decode_attn(q, kp, vp, bt, cu, Ls, 1, D ** -0.5, out, stream, n_split, ws)
+    for _ in range(7):
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        ev[0].record()
+        graph.replay()
+        ev[1].record()
+        torch.cuda.synchronize()
+        times.append(ev[0].elapsed_time(ev[1]) * 20)
+    return sorted(times)[3]
 
 
 def _check(D, Hq, Hkv, B, L_max, rows, call):
