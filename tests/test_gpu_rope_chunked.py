@@ -137,8 +137,10 @@ def test_chunked_prefill_against_oracle(budget, use_rope):
     torch.cuda.synchronize()
     S = wl.seq_lens - c
     assert n_steps == len(chunk_schedule(S, budget)) == -(-int(S.sum()) // budget)
-    # each query row meets the same keys in the same tile order however the
-    # suffix is cut, so chunking does not change a single bit
+    # the table reaches under 1024 keys and no step is decode-shaped, so every
+    # step runs the persistent kernel: each query row meets the same keys in the
+    # same tile order however the suffix is cut, and no bit changes (wider
+    # tables: test_chunked_prefill_over_a_wider_table)
     one = torch.empty_like(out)
     pc2 = _setup("llama8b", 12, 500000.0 if use_rope else None)[1]
     pc2.prefill_chunked(c, t, wl.seq_lens, rows["q"], rows["k_new"], rows["v_new"], one, wl.spec.scale,
@@ -158,3 +160,39 @@ def test_chunked_prefill_against_oracle(budget, use_rope):
     mean = tot / cnt
     log(f"[chunked] budget {budget} rope {use_rope}: {n_steps} steps max_abs={worst:.3e} mean_abs={mean:.3e}")
     assert worst <= MAX_ABS and mean <= MEAN_ABS
+
+
+def test_chunked_prefill_over_a_wider_table():
+    """Tables of 1024 keys, steps on both sides of the line (256 column tiles of
+    32) up to which the decode kernel takes them: the cuts need not agree bit
+    for bit.  Both kernels round the probabilities p to bf16 (2^-9 of each) and
+    the output (2^-9); sums are fp32.  So an output o = sum p v / sum p is off by
+    at most 2^-9 (A + |o|) with A = sum p |v| / sum p, and two cuts differ by
+    twice that; 5% is left for the fp32 scores and sums."""
+    wl, pc, c, t, _ = _setup("sweep50", 2)
+    assert max_blocks_of(wl) * BLOCK >= 1024
+    rows, S = wl.packed_suffix(c), wl.seq_lens - c
+    heads = wl.spec.n_kv_heads
+    G = wl.spec.n_q_heads // heads
+    outs, tiles = {}, set()
+    for budget in (1 << 30, 512, 257, 256, 64, 33):
+        for step in chunk_schedule(S, budget):
+            tiles.add(len(step) * heads * -(-max(n for _, _, n in step) * G // 32))
+        out = torch.empty_like(rows["q"])
+        pc2 = _setup("sweep50", 2)[1]
+        pc2.prefill_chunked(c, t, wl.seq_lens, rows["q"], rows["k_new"], rows["v_new"], out, wl.spec.scale, budget)
+        torch.cuda.synchronize()
+        outs[budget] = out.float().cpu().numpy()
+    assert min(tiles) < 256 and 256 in tiles and max(tiles) > 512
+    cu, worst, apart = rows["cu"], 0.0, 0.0
+    for r in range(len(wl.prompts)):
+        P, L = int(c[r]), int(wl.seq_lens[r])
+        q = wl.q_rows(r, P, L).float().cpu().numpy()
+        k, v = (x.float().cpu().numpy() for x in wl.dense_kv(r, L))
+        ref = prefill_attention_ref(q, k, v, wl.spec.scale)
+        bound = 1.05 * 2.0 ** -9 * (prefill_attention_ref(q, k, np.abs(v), wl.spec.scale) + np.abs(ref))
+        got = {b: o[int(cu[r]):int(cu[r + 1])] for b, o in outs.items()}
+        worst = max(worst, *(float((np.abs(o - ref) / bound).max()) for o in got.values()))
+        apart = max(apart, *(float((np.abs(o - got[1 << 30]) / bound).max()) for o in got.values()))
+    log(f"[chunked] 1024-key tables, 6 cuts: error up to {worst:.2f} of its bound, cuts up to {apart:.2f} apart")
+    assert worst <= 1 and apart <= 2
