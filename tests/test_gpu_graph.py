@@ -1,9 +1,9 @@
 """GPU: decode steps captured as a HIP graph (pipeline.DecodeGraph) replay to
 exactly the eager results, replay after replay with eager work in between,
-on both decode paths (the one-wave-per-pair kernel and the persistent kernel
-with its work-queue workspace), and agree with the fp64 oracle.  The same
+on two cuts of the keys over waves, and agree with the fp64 oracle.  The same
 holds for the scheduler steps of a chunked prefill (pipeline.ChunkGraph),
-with and without RoPE in the append.
+with and without RoPE in the append, their items handed out by position and
+from the counters in the workspace.
 """
 import sys
 
@@ -37,8 +37,8 @@ def log(*a):
     conftest.PARITY_LINES.append(" ".join(str(x) for x in a))
 
 
-# 16 prompts x 8 kv heads = 128 pairs (fewer than the compute units: the
-# persistent kernel); 64 prompts: 512 pairs (the decode kernel)
+# 16 prompts x 8 kv heads = 128 pairs (fewer than the compute units: several
+# waves to a pair); 64 prompts: 512 pairs
 @pytest.mark.parametrize("n_prompts", [16, 64])
 def test_decode_graph_replays_equal_eager(n_prompts):
     wl = workload.build(workload.scaled_spec("sweep100_decode", n_prompts, decode_steps=6))
@@ -95,8 +95,13 @@ def test_decode_graph_replays_equal_eager(n_prompts):
     log(f"[graph] {sp.name}: {dec} captured decode steps, 3 replays equal to eager, oracle max_abs={worst:.3e}")
 
 
-@pytest.mark.parametrize("budget,rope", [(1024, False), (300, True)])
-def test_chunk_graph_replays_equal_eager(budget, rope):
+# One step of 24 prompts is about 1900 items (short launches' counters); of 40
+# prompts of 1024 new tokens 10240 (a counted launch, in the wide layout).
+@pytest.mark.parametrize("budget,rope,name,n_prompts", [
+    (1024, False, "llama8b", 24), (300, True, "llama8b", 24), (1 << 20, False, "llama8b", 24),
+    (1 << 20, False, "sweep0", 40),
+])
+def test_chunk_graph_replays_equal_eager(budget, rope, name, n_prompts):
     """The steps of a chunked prefill captured as one graph (pipeline.ChunkGraph):
     every replay equals the eager chunked run bit for bit, with eager work on
     the default stream between replays, and agrees with the fp64 oracle."""
@@ -104,19 +109,20 @@ def test_chunk_graph_replays_equal_eager(budget, rope):
     from oracle.rope_ref import rope
     from paper_2507_08523_amd.pipeline import ChunkGraph, rope_inv_freq
 
-    wl = workload.build(workload.scaled_spec("llama8b", 24))
+    wl = workload.build(workload.scaled_spec(name, n_prompts))
     wl.materialize("cuda")
     sp = wl.spec
     pc = PagedPrefixCache(sp.n_kv_heads, sp.head_dim, pool_blocks_needed(wl), max_blocks_of(wl),
                           max(len(wl.prompts), len(wl.warm)), 16)
     inv = torch.from_numpy(rope_inv_freq(sp.head_dim, 5e5)).cuda() if rope else None
-    c, t = pc.match(wl.warm)
-    rows = wl.packed_warm(c)
-    b = pc.upload_prefill(c, t, [len(p) for p in wl.warm])
-    if rope:
-        pc.append_rope(b, rows["k_new"], rows["v_new"], inv)
-    else:
-        pc.append(b, rows["k_new"], rows["v_new"])
+    if wl.warm:
+        c, t = pc.match(wl.warm)
+        rows = wl.packed_warm(c)
+        b = pc.upload_prefill(c, t, [len(p) for p in wl.warm])
+        if rope:
+            pc.append_rope(b, rows["k_new"], rows["v_new"], inv)
+        else:
+            pc.append(b, rows["k_new"], rows["v_new"])
     c, t = pc.match(wl.prompts)
     rows = wl.packed_suffix(c)
     L = wl.seq_lens.astype(np.int32)
@@ -160,5 +166,5 @@ def test_chunk_graph_replays_equal_eager(budget, rope):
         err = np.abs(got - ref)
         assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, r
         worst = max(worst, float(err.max()))
-    log(f"[graph] chunked prefill llama8b[24] budget {budget}{' rope' if rope else ''}: {n} steps, "
+    log(f"[graph] chunked prefill {sp.name} budget {budget}{' rope' if rope else ''}: {n} steps, "
         f"3 replays bit-identical, max_abs={worst:.3e}")

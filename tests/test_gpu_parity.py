@@ -405,7 +405,7 @@ def test_abi_rejects_bad_arguments_on_device():
 
 def test_work_queue_workspace_reused_and_left_zeroed():
     # The persistent attention kernel hands out work items from counters in the
-    # workspace and the last workgroup clears them: back-to-back calls on one
+    # workspace and clears them itself: back-to-back calls on one
     # workspace, and calls on a second stream with their own workspace, give
     # identical outputs and leave every workspace zero-filled.
     run = Run("qwen7b")
