@@ -245,14 +245,14 @@ int ilpc_rope_kv_append(const uint16_t* q, uint16_t* q_out, int32_t Hq, const ui
  * max_q_len * (Hq / Hkv) <= 32 (ILPC_EUNSUP otherwise).  One wave per
  * (request, kv head) pair -- more where the pairs are too few to fill the
  * chip, each a range of the keys -- streams that request's K/V blocks from the
- * pools;
- * results agree with ilpc_paged_prefill_attn to the attention tolerance, not
- * bit for bit.  ilpc_paged_prefill_attn takes this path by itself for such
- * batches, as for n_split = 0 but with no more workgroups a pair than its
- * workspace has room for partial results; and for longer queries with few columns in the whole batch
- * (B * Hkv * ceil(max_q_len * Hq / Hkv / 32) at most the device's compute
- * units, at D = 64 twice as many) over contexts that may reach 1024 keys
- * (16 * max_blocks).
+ * pools.  ilpc_paged_prefill_attn takes this path by itself for such batches,
+ * as for n_split = 0 but with no more workgroups a pair than its workspace has
+ * room for partial results; and for longer queries with few columns in the
+ * whole batch (B * Hkv * ceil(max_q_len * Hq / Hkv / 32) at most the device's
+ * compute units, at D = 64 twice as many) over contexts that may reach 1024
+ * keys (16 * max_blocks).  The results of one query row under both kernels, or
+ * under different ranges of its keys, agree to the attention tolerance, not
+ * bit for bit; under one kernel and one cut of the keys they are the same bits.
  *
  * n_split      [host] key ranges per pair, 1 .. 64, or 0 for the library's
  *                     choice.  With n > 1 a pair's keys are cut into at least
@@ -370,16 +370,20 @@ int ilpc_attn_cascade_workspace_bytes(int32_t B, int32_t max_q_len, int32_t Hq, 
  * The same attention as ilpc_paged_prefill_attn, split at a prefix that every
  * request of the batch shares (the instruction and leading demonstrations of
  * the log-parsing prompts, section 2.1.1, which prefix caching stores once,
- * section 2.1.2): the shared keys are read once per 256 query columns of the
+ * section 2.1.2): the shared keys are read once per 128 query columns of the
  * whole batch (query row x q head of a kv head), not once per request.
- *   - Prefill-shaped batches (max_q_len * Hq / Hkv >= 64) whose shared prefix
+ *   - Batches of few query columns over long contexts that
+ *     ilpc_paged_prefill_attn gives to the decode kernel run there, unsplit:
+ *     with so few columns the sharing saves less than the idle compute units
+ *     cost.
+ *   - Other prefill-shaped batches (max_q_len * Hq / Hkv >= 64) whose shared prefix
  *     holds at least three 64-key tiles, and whose per-item tile list fits
- *     ((256 / G + 1) * (ceil(16 * max_blocks / 64) - floor(shared_len / 64))
- *     <= 2048, G = Hq / Hkv), run as one launch: each workgroup takes 256
+ *     ((ceil(128 / G) + 1) * (ceil(16 * max_blocks / 64) - floor(shared_len / 64))
+ *     <= 2048, G = Hq / Hkv), run as one launch: each workgroup takes 128
  *     columns of the batch, attends them to the floor(shared_len / 64) * 64
  *     shared keys, then to each of their requests' own keys from there on
  *     (masked to that request's columns, causal), in one online softmax.
- *   - Other batches (decode steps among them) run two launches: every query
+ *   - The rest (decode steps among them) run two launches: every query
  *     row over keys 0 .. shared_len-1, with the unnormalised state in the
  *     workspace, then each request's queries over its keys shared_len ..
  *     L_r-1, continuing from that state.

@@ -5,8 +5,8 @@
 // forbid allocation).
 //
 // The array holds the attention kernel's work-queue counters in its first 64
-// bytes (zero when the code object is loaded; every call's last workgroup
-// leaves them zero again) and, after them, room for the split decode kernel's
+// bytes (zero when the code object is loaded; every call leaves them zero
+// again) and, after them, room for the split decode kernel's
 // partial results.  Each GPU holds its own copy until the process ends, and
 // every call on a GPU shares it, so calls that may overlap on one GPU race.
 // In host code `scratch` names only the host-side stand-in of the device

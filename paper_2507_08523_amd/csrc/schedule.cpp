@@ -98,13 +98,16 @@ extern "C" int ilpc_shared_prefix_len(const int32_t* cached_len, const int32_t* 
 }
 
 // Measured on MI355X against the single pass: sweep100's prefill (976 shared
-// keys, 48 own) 9% faster in one launch; sweep75 (736 shared, 288 own) 3%
-// slower; llama8b and qwen7b (256 / 512 shared, 300-700 own) 9-12% slower.
-// The split removes no matrix-core work; it pays only where the shared keys
-// dominate and each request's own keys past them fit in two 64-key tiles.
+// keys, 48 own) 10% faster in one launch (129 -> 116 us); sweep75 (736 shared,
+// 288 own) 2% slower (631 -> 643); llama8b and qwen7b (256 / 512 shared, 300-700
+// own) 7-11% slower (225 -> 242, 2027 -> 2254).  The split removes no
+// matrix-core work; it pays only where the shared keys dominate and each
+// request's own keys past them fit in two 64-key tiles.
 // Decode-shaped batches (at most 32 query columns per request and kv head)
 // keep the single pass: the decode kernel reads a shared prefix from L2 per
-// request (sweep100's decode steps: 47 us single, 72 us split).
+// request and cuts few requests' keys over idle CUs, which the split does not
+// (sweep100's decode steps, 128 requests and most of the keys shared, the best
+// case for it: 45 us single, 42 us split, in two launches).
 extern "C" int ilpc_prefer_shared_split(const int32_t* seq_lens, int32_t B, int32_t max_q_len, int32_t Hq,
                                         int32_t Hkv, int32_t shared_len, int32_t* use) {
   static const char* fn = "ilpc_prefer_shared_split";
